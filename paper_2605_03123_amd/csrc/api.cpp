@@ -265,7 +265,7 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
       }
     }
     // upload ring
-    P->slot_bytes = (size_t)4 << 20;
+    P->slot_bytes = (size_t)6 << 20;
     if (fault_hit("alloc") ||
         hipHostMalloc((void**)&P->h_ring, P->slot_bytes * ffx_plan_s::kSlots, hipHostMallocDefault) != hipSuccess)
       throw Error(FFX_ENOMEM, "pinned host allocation failed");
@@ -1095,8 +1095,25 @@ void build_ham_action(ffx_plan_s& P, const DFHost& df, const double* h, DecompPo
       double* tA = (double*)A.alloc((size_t)P.dim[0] * 8);
       double* tB = (double*)A.alloc((size_t)P.dim[1] * 8);
       double* tV = (double*)A.alloc((size_t)N * P.dim[1] * 8);
-      dev::DiagSpecDev spec{nullptr, nullptr, dJ, dJ, dJ};
-      dev::diag_tables(P.d_masks[0], P.dim[0], P.d_masks[1], P.dim[1], N, spec, tA, tB, tV, s);
+      // (row p of V is linear in the beta occupations, with the coefficients J[p])
+      std::vector<dev::DiagJobDev> jobs((size_t)N + 2);
+      for (int k = 0; k < N + 2; ++k) {
+        dev::DiagJobDev& j = jobs[k];
+        j = dev::DiagJobDev{};
+        const int spin = k == 0 ? 0 : 1;
+        j.masks = P.d_masks[spin];
+        j.n = (int)P.dim[spin];
+        if (k < 2) {
+          j.Q = dJ;
+          j.val = k == 0 ? tA : tB;
+        } else {
+          j.lin = dJ + (size_t)(k - 2) * N;
+          j.val = tV + (size_t)(k - 2) * P.dim[1];
+        }
+      }
+      auto* dj = (dev::DiagJobDev*)A.alloc(jobs.size() * sizeof(dev::DiagJobDev));
+      HIPCHK(hipMemcpy(dj, jobs.data(), jobs.size() * sizeof(dev::DiagJobDev), hipMemcpyHostToDevice));
+      dev::string_tables(dj, N + 2, (int)std::max(P.dim[0], P.dim[1]), N, s);
       check_launch();
       A.diag = dev::OneBodyDiag{tA, tB, tV, P.d_masks[0], N};
     }

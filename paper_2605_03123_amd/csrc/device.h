@@ -46,15 +46,30 @@ struct DiagDev {
   const double* V;  // may be null (no cross term)
 };
 
-// Parameters for building DiagDev tables from occupation vectors:
-//   A[i] = lin_a . x + 1/2 x^T Q_a x,  B[i] = lin_b . x + 1/2 x^T Q_b x,
-//   V[p][i_b] = (C x_b)[p].  Any matrix pointer may be null (= zero).
+// Parameters for building per-string tables from occupation vectors:
+//   A[i] = lin_a . x + 1/2 x^T Q_a x,  B[i] = lin_b . x + 1/2 x^T Q_b x.
+// Any pointer may be null (= zero).
 struct DiagSpecDev {
   const double* lin_a;
   const double* lin_b;
   const double* Qa;
   const double* Qb;
-  const double* C;
+};
+
+// One per-string table: v(i) = lin . x_i + 1/2 x_i^T Q x_i for the n strings of
+// `masks`; written to val, or as a column phase factor
+//   colf[i] = (-1)^{|mask_i & sign|} exp(i (scale v(i) + sum_{q in mask_i} delta[q])),
+// or both.  lin, Q, delta, val and colf may each be null.
+struct DiagJobDev {
+  const uint32_t* masks;
+  const double* lin;
+  const double* Q;
+  double* val;
+  double* colf;  // complex (re, im)
+  const double* delta;
+  double scale;
+  int n;
+  uint32_t sign;
 };
 
 // Register window of the Givens passes: W = 6 for both precisions (complex64
@@ -71,9 +86,8 @@ void win_pass(bool c64, bool real, int spin, void* vec, int64_t dim_a, int64_t d
 void string_phase(bool c64, const uint32_t* masks, int64_t n, const double* delta, int norb,
                   void* phase, hipStream_t stream);
 
-void diag_tables(const uint32_t* masks_a, int64_t dim_a, const uint32_t* masks_b, int64_t dim_b,
-                 int norb, const DiagSpecDev& spec, double* A, double* B, double* V,
-                 hipStream_t stream);
+// every table of a program in one launch; jobs: n_jobs descriptions in device memory, max_n: the most strings of one
+void string_tables(const DiagJobDev* jobs, int n_jobs, int max_n, int norb, hipStream_t stream);
 
 // vec *= exp(i * scale * f)
 void diag_phase(bool c64, void* vec, int64_t dim_a, int64_t dim_b, const uint32_t* masks_a,
@@ -285,10 +299,6 @@ struct SegDev {
   int cross_lo, cross_cnt, cross_peer, cross_role;
   int pad;
 };
-
-// colf[i] = (-1)^{|mask_i & sign|} exp(i (scale B[i] + sum_{q in mask_i} delta[q]))
-void column_factors(const uint32_t* masks, int64_t n, const double* B, double scale, const double* delta,
-                    uint32_t sign, double* colf, hipStream_t stream);
 
 enum SegMode { SEG_STORE = 0, SEG_ACCUM = 1, SEG_NONE = 2 };
 

@@ -234,52 +234,57 @@ void string_phase(bool c64, const uint32_t* masks, int64_t n, const double* delt
     hipLaunchKernelGGL(k_string_phase<double>, grid, dim3(256), 0, s, masks, n, delta, norb, (zc128*)phase);
 }
 
-__global__ void k_diag_tables(const uint32_t* __restrict__ ma, int64_t da, const uint32_t* __restrict__ mb,
-                              int64_t db, int norb, DiagSpecDev sp, double* __restrict__ A,
-                              double* __restrict__ B, double* __restrict__ V) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < da && A) {
-    uint32_t m = ma[i];
-    double acc = 0;
-    for (int p = 0; p < norb; ++p) {
-      if (!((m >> p) & 1)) continue;
-      if (sp.lin_a) acc += sp.lin_a[p];
-      if (sp.Qa)
-        for (int q = 0; q < norb; ++q)
-          if ((m >> q) & 1) acc += 0.5 * sp.Qa[p * norb + q];
-    }
-    A[i] = acc;
+// Every per-string table of a program in one launch: block (x, job) takes 256
+// strings of one job, with the job's matrix and vectors staged in LDS (one
+// trip to memory for the whole block), and a thread walks the occupied
+// orbitals of its string.  Bound by that walk's chain (n^2 dependent FP64
+// additions in a fixed order) and the launch: one launch per table, each
+// thread reading the matrix from memory in a loop over all N^2 entries, took
+// 10 to 40 us per table at 8 to 16 orbitals (0.33 ms of a 2.0 ms DF step at
+// 12 orbitals with 12 terms); together they take about as long as one.
+constexpr int kMaxOrb = 32;
+__global__ __launch_bounds__(256) void k_string_tables(const DiagJobDev* __restrict__ jobs, int norb) {
+  __shared__ double q[kMaxOrb * kMaxOrb];
+  __shared__ double lin[kMaxOrb], delta[kMaxOrb];
+  const DiagJobDev job = uniform_load(jobs + blockIdx.y);
+  if ((int)(blockIdx.x * 256) >= job.n) return;  // the whole block: jobs differ in length
+  const int tid = threadIdx.x;
+  const int i = blockIdx.x * 256 + tid;
+  if (job.Q)
+    for (int e = tid; e < norb * norb; e += 256) q[e] = job.Q[e];
+  if (tid < norb) {
+    lin[tid] = job.lin ? job.lin[tid] : 0.0;
+    delta[tid] = job.delta ? job.delta[tid] : 0.0;
   }
-  if (i < db) {
-    uint32_t m = mb[i];
-    if (B) {
-      double acc = 0;
-      for (int p = 0; p < norb; ++p) {
-        if (!((m >> p) & 1)) continue;
-        if (sp.lin_b) acc += sp.lin_b[p];
-        if (sp.Qb)
-          for (int q = 0; q < norb; ++q)
-            if ((m >> q) & 1) acc += 0.5 * sp.Qb[p * norb + q];
-      }
-      B[i] = acc;
+  const uint32_t m = i < job.n ? job.masks[i] : 0u;
+  __syncthreads();
+  if (i >= job.n) return;
+  double acc = 0;
+  for (uint32_t x = m; x; x &= x - 1) {
+    const int p = __builtin_ctz(x);
+    if (job.lin) acc += lin[p];
+    if (job.Q)
+      for (uint32_t y = m; y; y &= y - 1) acc += 0.5 * q[p * norb + __builtin_ctz(y)];
+  }
+  if (job.val) job.val[i] = acc;
+  if (job.colf) {
+    double ang = job.lin || job.Q ? job.scale * acc : 0.0;
+    if (job.delta)
+      for (uint32_t x = m; x; x &= x - 1) ang += delta[__builtin_ctz(x)];
+    zc128 f = phase_factor<double>(ang);
+    if (parity(m & job.sign)) {
+      f.x = -f.x;
+      f.y = -f.y;
     }
-    if (V && sp.C) {
-      for (int p = 0; p < norb; ++p) {
-        double acc = 0;
-        for (int q = 0; q < norb; ++q)
-          if ((m >> q) & 1) acc += sp.C[p * norb + q];
-        V[(int64_t)p * db + i] = acc;
-      }
-    }
+    ((zc128*)job.colf)[i] = f;
   }
 }
 
-void diag_tables(const uint32_t* masks_a, int64_t dim_a, const uint32_t* masks_b, int64_t dim_b,
-                 int norb, const DiagSpecDev& spec, double* A, double* B, double* V,
-                 hipStream_t s) {
-  int64_t n = dim_a > dim_b ? dim_a : dim_b;
-  hipLaunchKernelGGL(k_diag_tables, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, masks_a, dim_a,
-                     masks_b, dim_b, norb, spec, A, B, V);
+void string_tables(const DiagJobDev* jobs, int n_jobs, int max_n, int norb, hipStream_t s) {
+  // (grid.y holds at most 65535 jobs)
+  for (int j0 = 0; j0 < n_jobs; j0 += 65535)
+    hipLaunchKernelGGL(k_string_tables, dim3((unsigned)((max_n + 255) / 256), (unsigned)std::min(n_jobs - j0, 65535)),
+                       dim3(256), 0, s, jobs + j0, norb);
 }
 
 // ---------------------------------------------------------------------------

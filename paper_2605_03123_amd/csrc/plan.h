@@ -311,11 +311,13 @@ struct TableBuild {
   dev::DiagSpecDev spec;
   double* A;  // per alpha string
   double* B;  // per beta string
+  bool used[2];  // A, B: read by a stage
 };
 
 struct ColfBuild {
   int spin;          // column spin: its configuration masks
-  const double* B;   // per-string table (nullable)
+  int diag;          // the diagonal function whose table of that spin it takes (-1: none)
+  const double* B;   // that table (nullable)
   double scale;
   const double* delta;
   uint32_t sign;
@@ -325,6 +327,9 @@ struct ColfBuild {
 struct Compiled {
   std::vector<TableBuild> tables;
   std::vector<ColfBuild> colfs;
+  // the tables as device jobs, built by one launch before the first pass
+  const dev::DiagJobDev* jobs = nullptr;
+  int n_jobs = 0, jobs_max_n = 0;
   std::vector<Launch> launches;
   int final_mode = FINAL_STORE;
 };

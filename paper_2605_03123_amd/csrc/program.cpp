@@ -276,9 +276,11 @@ Compiled compile_program(ffx_plan_s& P, Upload& up, const Program& prog, int fin
     const int cs = colspin();
     ColfBuild cb{};
     cb.spin = cs;
+    cb.diag = diag;
     cb.scale = scale;
     if (diag >= 0) {
-      const TableBuild& tb = c.tables[diag];
+      TableBuild& tb = c.tables[diag];
+      tb.used[rowspin()] = true;  // (the column spin's values go into the column factors)
       st.A = layout == 0 ? tb.A : tb.B;
       st.C = layout == 0 ? Cd[diag] : CTd[diag];
       cb.B = layout == 0 ? tb.B : tb.A;
@@ -316,7 +318,8 @@ Compiled compile_program(ffx_plan_s& P, Upload& up, const Program& prog, int fin
     dev::StageDev st{};
     st.type = type;
     if (diag >= 0) {
-      const TableBuild& tb = c.tables[diag];
+      TableBuild& tb = c.tables[diag];
+      tb.used[0] = tb.used[1] = true;
       st.A = layout == 0 ? tb.A : tb.B;
       st.B = layout == 0 ? tb.B : tb.A;
       st.C = layout == 0 ? Cd[diag] : CTd[diag];
@@ -555,6 +558,41 @@ Compiled compile_program(ffx_plan_s& P, Upload& up, const Program& prog, int fin
     fused.push_back(L);
   }
   c.launches = std::move(fused);
+  // the tables as jobs of one launch: the per-string values that some stage
+  // reads, and the column factors, which take the values they need from the
+  // diagonal function itself rather than from its table (no order between
+  // jobs).  (Batched programs take the lists above: their tables are tasks.)
+  if (!P.arena_hook) {
+    std::vector<dev::DiagJobDev> jobs;
+    auto job = [&](int spin, const dev::DiagSpecDev* spec) {
+      dev::DiagJobDev j{};
+      j.masks = P.d_masks[spin];
+      j.n = (int)P.dim[spin];
+      if (spec) {
+        j.lin = spin == 0 ? spec->lin_a : spec->lin_b;
+        j.Q = spin == 0 ? spec->Qa : spec->Qb;
+      }
+      c.jobs_max_n = std::max(c.jobs_max_n, j.n);
+      return j;
+    };
+    for (const TableBuild& tb : c.tables)
+      for (int spin = 0; spin < 2; ++spin) {
+        if (!tb.used[spin]) continue;
+        dev::DiagJobDev j = job(spin, &tb.spec);
+        j.val = spin == 0 ? tb.A : tb.B;
+        jobs.push_back(j);
+      }
+    for (const ColfBuild& cb : c.colfs) {
+      dev::DiagJobDev j = job(cb.spin, cb.diag >= 0 ? &c.tables[cb.diag].spec : nullptr);
+      j.colf = cb.out;
+      j.scale = cb.scale;
+      j.delta = cb.delta;
+      j.sign = cb.sign;
+      jobs.push_back(j);
+    }
+    c.n_jobs = (int)jobs.size();
+    if (c.n_jobs > 0) c.jobs = up.put(jobs.data(), jobs.size());
+  }
   return c;
 }
 
@@ -562,12 +600,8 @@ void execute_program(ffx_plan_s& P, const Compiled& c, const void* src, void* wo
                      hipStream_t s) {
   const int64_t da = P.dim[0], db = P.dim[1];
   const int N = P.norb;
-  for (const TableBuild& tb : c.tables) {
-    dev::diag_tables(P.d_masks[0], da, P.d_masks[1], db, N, tb.spec, tb.A, tb.B, nullptr, s);
-    check_launch();
-  }
-  for (const ColfBuild& cb : c.colfs) {
-    dev::column_factors(P.d_masks[cb.spin], P.dim[cb.spin], cb.B, cb.scale, cb.delta, cb.sign, cb.out, s);
+  if (c.n_jobs > 0) {
+    dev::string_tables(c.jobs, c.n_jobs, c.jobs_max_n, N, s);
     check_launch();
   }
   int last_seg = -1;

@@ -634,34 +634,6 @@ void seg_pass_planes(int W, int threads, const SegPassDev& p, size_t lds, hipStr
     planes_w<512>(W, p, lds, s);
 }
 
-__global__ void k_column_factors(const uint32_t* __restrict__ masks, int64_t n, const double* __restrict__ B,
-                                 double scale, const double* __restrict__ delta, uint32_t sign,
-                                 zc128* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint32_t m = masks[i];
-  double ang = B ? scale * B[i] : 0.0;
-  if (delta) {
-    uint32_t x = m;
-    while (x) {
-      ang += delta[__builtin_ctz(x)];
-      x &= x - 1;
-    }
-  }
-  zc128 f = phase_factor<double>(ang);
-  if (parity(m & sign)) {
-    f.x = -f.x;
-    f.y = -f.y;
-  }
-  out[i] = f;
-}
-
-void column_factors(const uint32_t* masks, int64_t n, const double* B, double scale, const double* delta,
-                    uint32_t sign, double* colf, hipStream_t s) {
-  hipLaunchKernelGGL(k_column_factors, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, masks, n, B, scale,
-                     delta, sign, (zc128*)colf);
-}
-
 size_t seg_pass_lds(bool c64, int max_len, int max_mt) {
   size_t row = (size_t)max_len * (c64 ? 8 : 16);
   row = (row + 15) & ~(size_t)15;
