@@ -241,29 +241,6 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
       int w = std::atoi(e);
       if (w >= 1 && w < P->W) P->W = w;
     }
-    for (int s = 0; s < 2; ++s) {
-      for (int a = 0; a + P->W <= norb; ++a) {
-        WindowTable t = build_window_table(P->str[s], norb, P->n[s], a, P->W);
-        dev::WinDev wd{};
-        int* tab = (int*)P->dalloc(t.tab.size() * 4);
-        int* cm = (int*)P->dalloc(t.chunk_m.size() * 4);
-        int* co = (int*)P->dalloc(t.chunk_off.size() * 4);
-        int* cl = (int*)P->dalloc(t.cls.size() * 4);
-        HIPCHK(hipMemcpy(tab, t.tab.data(), t.tab.size() * 4, hipMemcpyHostToDevice));
-        HIPCHK(hipMemcpy(cm, t.chunk_m.data(), t.chunk_m.size() * 4, hipMemcpyHostToDevice));
-        HIPCHK(hipMemcpy(co, t.chunk_off.data(), t.chunk_off.size() * 4, hipMemcpyHostToDevice));
-        HIPCHK(hipMemcpy(cl, t.cls.data(), t.cls.size() * 4, hipMemcpyHostToDevice));
-        wd.tab = tab;
-        wd.chunk_m = cm;
-        wd.chunk_off = co;
-        wd.cls = cl;
-        wd.n_chunks = (int)t.chunk_m.size();
-        wd.n_cls = (int)t.cls.size();
-        wd.a = a;
-        wd.w = P->W;
-        P->win[s].push_back(wd);
-      }
-    }
     // upload ring
     P->slot_bytes = (size_t)6 << 20;
     if (fault_hit("alloc") ||
@@ -292,7 +269,7 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
     // segments fit in LDS together with the stage tables and the member
     // offset tables of every register window inside the segment
     const size_t lds_cap = 160 * 1024 - 64;
-    int64_t max_elems = (int64_t)((lds_cap - dev::seg_pass_lds(P->c64, 0, 0)) / P->elem());
+    int64_t max_elems = (int64_t)((lds_cap - dev::seg_pass_lds(P->c64, norb, 0, 0, false)) / P->elem());
     // the row-pair transition one-body kernel (the path above 16 orbitals) at
     // any size, for tests
     P->rdm_pairs = std::getenv("FFX_RDM_PAIRS") != nullptr;
@@ -338,6 +315,102 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
     const bool planes_all = std::getenv("FFX_PLANES_ALL") != nullptr;
     const char* pack_env = std::getenv("FFX_SEG_PACK");
     const bool pack_ok = !(pack_env && std::atoi(pack_env) == 0);
+    int cus = 256;
+    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
+    // a diagonal stage tabulates its cross term by bytes of the column string;
+    // segments shorter than the tables evaluate it per element
+    auto evaluates_directly = [&](int64_t longest) { return longest < 256 * ((norb + 7) / 8); };
+    // Threads of a block: the waves that the registers leave a compute unit
+    // (max_threads / 64), shared by the blocks that its LDS holds (or by the
+    // fewer that the launch has for it), and no more than the widest window's
+    // chunks or four elements a thread can use.  At 14 orbitals a row of
+    // complex128 leaves room for two blocks: 256-thread blocks, one to a unit
+    // with 32-bit member tables beside the row, ran 963 us per pass.
+    auto block_threads = [&](const std::vector<std::vector<SegWindowTable>>& tabs, size_t lds, int64_t blocks,
+                             int max_threads, int max_len) {
+      size_t chunks = 1;
+      for (const auto& ts : tabs)
+        for (const SegWindowTable& t : ts) chunks = std::max(chunks, t.chunk_m.size());
+      const int64_t room = std::max<int64_t>(1, (int64_t)(160 * 1024 / std::max<size_t>(lds, 1)));
+      const int64_t per_cu = std::max<int64_t>(1, std::min(room, (blocks + cus - 1) / cus));
+      int64_t waves = std::max<int64_t>(1, max_threads / 64 / per_cu);
+      waves = std::min<int64_t>(waves, std::max<int64_t>((int64_t)chunks, (max_len + 255) / 256));
+      // a whole number of waves per SIMD, where blocks share a compute unit: a
+      // block's waves start at the first SIMD, so two blocks of 6 waves need
+      // four places there and only three exist (14 orbitals, complex
+      // rotations: 770 us per pass against 600 with 4 waves)
+      if (per_cu > 1 && waves > 4) waves = waves / 4 * 4;
+      int t = (int)waves * 64;
+      if (const char* e = std::getenv("FFX_SEG_THREADS")) {  // block size override, for tuning
+        const int v = std::atoi(e);
+        if (v >= 64 && v <= 1024 && v % 64 == 0) t = v;
+      }
+      return std::min(t, max_threads);
+    };
+    // the class tables of every segment and register window on the device
+    // (wide: member offsets of 32 bits, for complex rotations of complex64);
+    // *max_mt: the most 16-byte words of member offsets of one segment
+    auto upload_windows = [&](const std::vector<std::pair<int, int>>& sg,
+                              const std::vector<std::vector<SegWindowTable>>& tabs, int W, int threads, bool wide,
+                              int* max_mt) {
+      // packed on the host and copied once
+      std::vector<char> blob;
+      auto put = [&](const void* src, size_t bytes) {
+        const size_t off = blob.size();
+        blob.resize(off + (bytes + 15) / 16 * 16);
+        if (bytes) std::memcpy(blob.data() + off, src, bytes);
+        return off;
+      };
+      struct Offs {
+        size_t code, chunk_m;
+        int n_chunks;
+      };
+      std::vector<std::vector<Offs>> offs(sg.size());
+      std::vector<size_t> mt_off(sg.size());
+      std::vector<dev::SegDev> out;
+      *max_mt = 0;
+      size_t n_wins = 0;
+      for (size_t g = 0; g < sg.size(); ++g) {
+        std::vector<uint16_t> mt;
+        std::vector<int> mt32;
+        for (SegWindowTable t : tabs[g]) {
+          balance_seg_window(t, W, threads / 64);
+          std::vector<int> codes;
+          if (wide) {
+            codes = pack_class_codes(t, (int)mt32.size());
+            mt32.insert(mt32.end(), t.mt.begin(), t.mt.end());
+            while (mt32.size() % 4) mt32.push_back(0);
+          } else {
+            t = compact_members(t, W, mt);
+            codes = pack_class_codes(t, 0);
+          }
+          offs[g].push_back({put(codes.data(), codes.size() * 4), put(t.chunk_m.data(), t.chunk_m.size() * 4),
+                             (int)t.chunk_m.size()});
+        }
+        n_wins += offs[g].size();
+        const int words = (int)(wide ? mt32.size() / 4 : mt.size() / 8);
+        mt_off[g] = wide ? put(mt32.data(), mt32.size() * 4) : put(mt.data(), mt.size() * 2);
+        *max_mt = std::max(*max_mt, words);
+        dev::SegDev d{};
+        d.off = sg[g].first;
+        d.len = sg[g].second;
+        d.n_mt_all = words;
+        out.push_back(d);
+      }
+      const size_t win0 = blob.size();
+      char* dev_base = (char*)P->dalloc(win0 + std::max<size_t>(n_wins, 1) * sizeof(dev::SegWinDev));
+      std::vector<dev::SegWinDev> wins;
+      for (size_t g = 0; g < sg.size(); ++g) {
+        out[g].win = (const dev::SegWinDev*)(dev_base + win0) + wins.size();
+        out[g].mt_all = (const int4*)(dev_base + mt_off[g]);
+        for (const Offs& o : offs[g])
+          wins.push_back({(const int*)(dev_base + o.code), (const int*)(dev_base + o.chunk_m), o.n_chunks, 0});
+      }
+      (void)put(wins.data(), wins.size() * sizeof(dev::SegWinDev));
+      if (!blob.empty())
+        HIPCHK(hipMemcpy(dev_base, blob.data(), win0 + wins.size() * sizeof(dev::SegWinDev), hipMemcpyHostToDevice));
+      return out;
+    };
     int max_rows_x_seg = 0;
     for (int s = 0; s < 2; ++s) {
       auto& ss = P->seg[s];
@@ -363,11 +436,14 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
           size_t mt_bound = 0;
           for (int a = 0; W0 >= 2 && a + W0 <= wt; ++a) {
             const size_t nl1 = (size_t)std::min(a, nc) + 1;
-            mt_bound = (mt_bound + 3) & ~(size_t)3;
-            mt_bound += (((size_t)(W0 + 1) * nl1 + 3) & ~(size_t)3);
-            for (int m = 0; m <= W0; ++m) mt_bound += nl1 * (((size_t)binom(W0, m) + 3) & ~(size_t)3);
+            if (P->c64) {  // 32-bit offsets and their index (the tables of complex rotations)
+              mt_bound += ((size_t)(W0 + 1) * nl1 + 3) / 4 + 1;
+              for (int m = 0; m <= W0; ++m) mt_bound += nl1 * (((size_t)binom(W0, m) + 3) / 4);
+            } else {
+              for (int m = 1; m < W0; ++m) mt_bound += nl1 * (((size_t)binom(W0, m) + 7) / 8);
+            }
           }
-          const size_t fixed = dev::seg_pass_lds(P->c64, 0, (int)mt_bound);
+          const size_t fixed = dev::seg_pass_lds(P->c64, norb, 0, (int)mt_bound, false);
           const int64_t cap = fixed < lds_cap ? std::min<int64_t>(max_elems, (int64_t)((lds_cap - fixed) / P->elem())) : 0;
           std::vector<std::pair<int, int>> groups = pack_runs(segs, cap);
           if (groups.size() * 4 <= segs.size() * 3) {
@@ -377,16 +453,23 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
         }
         const int Wseg = std::min(P->W, wt);
         tabs.assign(segs.size(), {});
+        longest = 0;
+        for (const auto& r : segs) longest = std::max<int64_t>(longest, r.second);
+        ss.direct = evaluates_directly(longest);
         size_t need = 0;
         for (size_t g = 0; g < segs.size(); ++g) {
           std::vector<uint64_t> sub(strs.begin() + segs[g].first, strs.begin() + segs[g].first + segs[g].second);
-          size_t mt = 0;
+          std::vector<uint16_t> mt;
+          size_t words = 0;
           for (int a = 0; Wseg >= 2 && a + Wseg <= wt; ++a) {
             tabs[g].push_back(build_seg_window(sub, wt, a, Wseg, lds_group));
-            mt = ((mt + 3) & ~(size_t)3) + tabs[g].back().mt.size();
+            (void)compact_members(tabs[g].back(), Wseg, mt);
+            if (P->c64) words += (tabs[g].back().mt.size() + 3) / 4;
           }
-          need = std::max(need, dev::seg_pass_lds(P->c64, segs[g].second, (int)mt));
+          words = std::max(words, mt.size() / 8);
+          need = std::max(need, dev::seg_pass_lds(P->c64, norb, segs[g].second, (int)words, ss.direct));
         }
+        ss.lds = need;
         if (need <= lds_cap) break;
       }
       if (wt < 0) throw Error(FFX_EUNSUPPORTED, "no segment window fits in LDS");
@@ -394,46 +477,27 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
       ss.Wseg = std::min(P->W, wt);
       ss.n_seg = (int)segs.size();
       ss.max_len = 0;
-      ss.max_mt = 0;
       for (const auto& sg : segs) ss.max_len = std::max(ss.max_len, sg.second);
-      ss.threads = ss.max_len >= 4096 ? 1024 : (ss.max_len >= 1024 ? 256 : 64);
-      if (const char* e = std::getenv("FFX_SEG_THREADS")) {  // block size override, for tuning
-        int v = std::atoi(e);
-        if (v >= 64 && v <= 1024 && v % 64 == 0) ss.threads = v;
-      }
-      ss.threads = dev::seg_pass_threads(P->c64, ss.Wseg, ss.threads);
-      std::vector<dev::SegDev> hsegs;
-      for (size_t g = 0; g < segs.size(); ++g) {
-        const auto& sg = segs[g];
-        ss.max_len = std::max(ss.max_len, sg.second);
-        std::vector<dev::SegWinDev> wins;
-        std::vector<int> mt_all;
-        for (SegWindowTable& t : tabs[g]) {
-          balance_seg_window(t, ss.Wseg, ss.threads / 64);
-          dev::SegWinDev wd{};
-          while (mt_all.size() % 4) mt_all.push_back(0);
-          wd.mt_off = (int)mt_all.size();
-          const std::vector<int> packed = pack_class_codes(t, wd.mt_off);
-          int* code = (int*)P->dalloc(std::max<size_t>(packed.size(), 1) * 4);
-          int* cm = (int*)P->dalloc(std::max<size_t>(t.chunk_m.size(), 1) * 4);
-          if (!packed.empty()) HIPCHK(hipMemcpy(code, packed.data(), packed.size() * 4, hipMemcpyHostToDevice));
-          if (!t.chunk_m.empty()) HIPCHK(hipMemcpy(cm, t.chunk_m.data(), t.chunk_m.size() * 4, hipMemcpyHostToDevice));
-          wd.code = code;
-          wd.chunk_m = cm;
-          wd.n_chunks = (int)t.chunk_m.size();
-          wd.nl1 = t.nl1;
-          mt_all.insert(mt_all.end(), t.mt.begin(), t.mt.end());
-          wins.push_back(wd);
+      const int64_t n_blocks = P->dim[1 - s] * (int64_t)ss.n_seg;
+      ss.threads = block_threads(tabs, ss.lds, n_blocks, dev::seg_pass_max_threads(P->c64, ss.Wseg, false), ss.max_len);
+      std::vector<dev::SegDev> hsegs = upload_windows(segs, tabs, ss.Wseg, ss.threads, P->c64, &ss.max_mt);
+      ss.lds = dev::seg_pass_lds(P->c64, norb, ss.max_len, ss.max_mt, ss.direct);
+      // tables for real rotations, at window width 6 with the parts of an
+      // amplitude in neighbouring lanes
+      const bool split = ss.Wseg == dev::kShapeW;
+      size_t real_words = 0;
+      for (auto& ts : tabs) {
+        std::vector<uint16_t> mt;
+        for (SegWindowTable& t : ts) {
+          if (split) t = split_seg_window(t, ss.Wseg);
+          (void)compact_members(t, ss.Wseg, mt);
         }
-        while (mt_all.size() % 4) mt_all.push_back(0);  // staged as int4 words
-        ss.max_mt = std::max(ss.max_mt, (int)mt_all.size());
-        auto* dw = (dev::SegWinDev*)P->dalloc(std::max<size_t>(wins.size(), 1) * sizeof(dev::SegWinDev));
-        if (!wins.empty())
-          HIPCHK(hipMemcpy(dw, wins.data(), wins.size() * sizeof(dev::SegWinDev), hipMemcpyHostToDevice));
-        int* dmt = (int*)P->dalloc(std::max<size_t>(mt_all.size(), 1) * 4);
-        if (!mt_all.empty()) HIPCHK(hipMemcpy(dmt, mt_all.data(), mt_all.size() * 4, hipMemcpyHostToDevice));
-        hsegs.push_back(dev::SegDev{sg.first, sg.second, dw, dmt, (int)mt_all.size(), 0, 0, 0, 0, 0});
+        real_words = std::max(real_words, mt.size() / 8);
       }
+      ss.lds_real = dev::seg_pass_lds(P->c64, norb, ss.max_len, (int)real_words, ss.direct);
+      ss.threads_real =
+          block_threads(tabs, ss.lds_real, n_blocks, dev::seg_pass_max_threads(P->c64, ss.Wseg, split), ss.max_len);
+      std::vector<dev::SegDev> hreal = upload_windows(segs, tabs, ss.Wseg, ss.threads_real, false, &ss.max_mt_real);
       // partner ranges of the crossing rotation on (wt - 1, wt): a segment whose
       // high part H lacks wt pairs its strings holding wt - 1 (the last C(wt-1,
       // k-1) of its C(wt, k)) with the first C(wt-1, k-1) strings of segment
@@ -451,17 +515,20 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
         const auto cr = crossing_ranges(strs, segs, wt, s == 0 ? na : nb);
         for (size_t g = 0; g < segs.size(); ++g) {
           if (!cr[g].has) continue;
-          dev::SegDev& d = hsegs[g];
-          d.cross_role = cr[g].role;
-          d.cross_lo = cr[g].lo;
-          d.cross_cnt = cr[g].cnt;
-          d.cross_peer = cr[g].peer;
+          for (auto* hs : {&hsegs, &hreal}) {
+            dev::SegDev& d = (*hs)[g];
+            d.cross_role = cr[g].role;
+            d.cross_lo = cr[g].lo;
+            d.cross_cnt = cr[g].cnt;
+            d.cross_peer = cr[g].peer;
+          }
           ss.cross = true;
         }
       }
       ss.d_segs = (dev::SegDev*)P->dalloc(hsegs.size() * sizeof(dev::SegDev));
       HIPCHK(hipMemcpy(ss.d_segs, hsegs.data(), hsegs.size() * sizeof(dev::SegDev), hipMemcpyHostToDevice));
-      ss.lds = dev::seg_pass_lds(P->c64, ss.max_len, ss.max_mt);
+      ss.d_real = (dev::SegDev*)P->dalloc(hreal.size() * sizeof(dev::SegDev));
+      HIPCHK(hipMemcpy(ss.d_real, hreal.data(), hreal.size() * sizeof(dev::SegDev), hipMemcpyHostToDevice));
       // rows of this column spin's layout times segments: one partial sum per block
       max_rows_x_seg = std::max<int>(max_rows_x_seg, (int)(P->dim[1 - s] * ss.n_seg));
       // complex128 rows split into segments: visits whose rotations are all
@@ -487,21 +554,19 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
           if (wp < norb && !(plane_seg_forced || (!packed && wp > ss.wt))) break;
           if (psegs.size() > 1 && Wp != 6) break;  // (the split-row plane kernel is built for width 6)
           std::vector<std::vector<SegWindowTable>> ptabs(psegs.size());
-          size_t mt_max = 0, n_tabs = 0;
+          size_t mt_max = 0;
           for (size_t g = 0; g < psegs.size(); ++g) {
             std::vector<uint64_t> sub(strs.begin() + psegs[g].first,
                                       strs.begin() + psegs[g].first + psegs[g].second);
-            size_t mt = 0;
+            std::vector<uint16_t> mt;
             for (int a = 0; a + Wp <= wp; ++a) {
               ptabs[g].push_back(build_seg_window(sub, wp, a, Wp, lds_group_bytes / 8));
-              mt = ((mt + 3) & ~(size_t)3) + ptabs[g].back().mt.size();
+              (void)compact_members(ptabs[g].back(), Wp, mt);
             }
-            mt_max = std::max(mt_max, mt);
-            n_tabs = std::max(n_tabs, ptabs[g].size());
+            mt_max = std::max(mt_max, mt.size() / 8);
           }
           // the row area holds 8-byte parts: sized as a complex64 row
-          const size_t need = dev::seg_pass_lds(true, (int)longest, (int)mt_max + 3 * (int)n_tabs + 4);
-          if (need > lds_cap) continue;
+          if (dev::seg_pass_lds(true, norb, (int)longest, (int)mt_max, false) > lds_cap) continue;
           auto& pl = P->plane[s];
           pl.wt = wp;
           pl.Wseg = Wp;
@@ -509,42 +574,10 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
           pl.max_len = (int)longest;
           pl.threads = plane_threads;
           pl.cross = false;
-          pl.max_mt = 0;
-          std::vector<dev::SegDev> hsegs;
-          for (size_t g = 0; g < psegs.size(); ++g) {
-            std::vector<dev::SegWinDev> wins;
-            std::vector<int> mt_all;
-            for (SegWindowTable& t : ptabs[g]) {
-              balance_seg_window(t, Wp, plane_threads / 64);
-              dev::SegWinDev wd{};
-              while (mt_all.size() % 4) mt_all.push_back(0);
-              wd.mt_off = (int)mt_all.size();
-              const std::vector<int> packed = pack_class_codes(t, wd.mt_off);
-              int* code = (int*)P->dalloc(std::max<size_t>(packed.size(), 1) * 4);
-              int* cm = (int*)P->dalloc(std::max<size_t>(t.chunk_m.size(), 1) * 4);
-              if (!packed.empty())
-                HIPCHK(hipMemcpy(code, packed.data(), packed.size() * 4, hipMemcpyHostToDevice));
-              if (!t.chunk_m.empty())
-                HIPCHK(hipMemcpy(cm, t.chunk_m.data(), t.chunk_m.size() * 4, hipMemcpyHostToDevice));
-              wd.code = code;
-              wd.chunk_m = cm;
-              wd.n_chunks = (int)t.chunk_m.size();
-              wd.nl1 = t.nl1;
-              mt_all.insert(mt_all.end(), t.mt.begin(), t.mt.end());
-              wins.push_back(wd);
-            }
-            while (mt_all.size() % 4) mt_all.push_back(0);
-            pl.max_mt = std::max(pl.max_mt, (int)mt_all.size());
-            auto* dw = (dev::SegWinDev*)P->dalloc(std::max<size_t>(wins.size(), 1) * sizeof(dev::SegWinDev));
-            if (!wins.empty())
-              HIPCHK(hipMemcpy(dw, wins.data(), wins.size() * sizeof(dev::SegWinDev), hipMemcpyHostToDevice));
-            int* dmt = (int*)P->dalloc(std::max<size_t>(mt_all.size(), 1) * 4);
-            if (!mt_all.empty()) HIPCHK(hipMemcpy(dmt, mt_all.data(), mt_all.size() * 4, hipMemcpyHostToDevice));
-            hsegs.push_back(dev::SegDev{psegs[g].first, psegs[g].second, dw, dmt, (int)mt_all.size(), 0, 0, 0, 0, 0});
-          }
+          std::vector<dev::SegDev> hsegs = upload_windows(psegs, ptabs, Wp, plane_threads, false, &pl.max_mt);
           pl.d_segs = (dev::SegDev*)P->dalloc(hsegs.size() * sizeof(dev::SegDev));
           HIPCHK(hipMemcpy(pl.d_segs, hsegs.data(), hsegs.size() * sizeof(dev::SegDev), hipMemcpyHostToDevice));
-          pl.lds = dev::seg_pass_lds(true, pl.max_len, pl.max_mt);
+          pl.lds = dev::seg_pass_lds(true, norb, pl.max_len, pl.max_mt, false);
           if (pl.lds > lds_cap) {
             pl = ffx_plan_s::SegSet{};
           } else {
@@ -552,6 +585,31 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
           }
           break;
         }
+      }
+    }
+    // class tables of the whole-spin window passes, which run where rotations cross segments
+    for (int s = 0; s < 2; ++s) {
+      if (P->seg[s].wt == norb && (P->plane[s].n_seg == 0 || P->plane[s].wt == norb)) continue;
+      for (int a = 0; a + P->W <= norb; ++a) {
+        WindowTable t = build_window_table(P->str[s], norb, P->n[s], a, P->W);
+        dev::WinDev wd{};
+        int* tab = (int*)P->dalloc(t.tab.size() * 4);
+        int* cm = (int*)P->dalloc(t.chunk_m.size() * 4);
+        int* co = (int*)P->dalloc(t.chunk_off.size() * 4);
+        int* cl = (int*)P->dalloc(t.cls.size() * 4);
+        HIPCHK(hipMemcpy(tab, t.tab.data(), t.tab.size() * 4, hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(cm, t.chunk_m.data(), t.chunk_m.size() * 4, hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(co, t.chunk_off.data(), t.chunk_off.size() * 4, hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(cl, t.cls.data(), t.cls.size() * 4, hipMemcpyHostToDevice));
+        wd.tab = tab;
+        wd.chunk_m = cm;
+        wd.chunk_off = co;
+        wd.cls = cl;
+        wd.n_chunks = (int)t.chunk_m.size();
+        wd.n_cls = (int)t.cls.size();
+        wd.a = a;
+        wd.w = P->W;
+        P->win[s].push_back(wd);
       }
     }
     if (max_rows_x_seg > P->n_partials) {

@@ -151,20 +151,23 @@ void build_tables(ffx_batch_s& b) {
       R = (int)std::min<int64_t>({(int64_t)R, (int64_t)64, std::max<int64_t>(nrows, 1)});
       t.rows_per_task[cs] = R;
       b.wq_rows = std::max(b.wq_rows, R);
-      std::vector<dev::SegWinDev> wins;
-      std::vector<int> mt_all;
+      std::vector<dev::SegWinDev> wins, wins_real;
+      std::vector<uint16_t> mt_real;
+      std::vector<int> mt_wide;  // 32-bit offsets: complex rotations of complex64
       for (int a = 0; ss.Wseg >= 2 && a + ss.Wseg <= ss.wt; ++a) {
-        SegWindowTable one = build_seg_window(P.str[cs], ss.wt, a, ss.Wseg);
-        SegWindowTable rep = replicate_seg_window(one, ss.Wseg, R, (int)len);
+        const SegWindowTable one = build_seg_window(P.str[cs], ss.wt, a, ss.Wseg);
+        const SegWindowTable rep = replicate_seg_window(one, ss.Wseg, R, (int)len);
         dev::SegWinDev wd{};
-        while (mt_all.size() % 4) mt_all.push_back(0);
-        wd.mt_off = (int)mt_all.size();
-        wd.code = b.upload_table(pack_class_codes(rep, wd.mt_off));
         wd.chunk_m = b.upload_table(rep.chunk_m);
         wd.n_chunks = (int)rep.chunk_m.size();
-        wd.nl1 = rep.nl1;
-        mt_all.insert(mt_all.end(), rep.mt.begin(), rep.mt.end());
-        wins.push_back(wd);
+        wd.code = b.upload_table(pack_class_codes(compact_members(rep, ss.Wseg, mt_real), 0));
+        wins_real.push_back(wd);
+        if (b.c64) {
+          wd.code = b.upload_table(pack_class_codes(rep, (int)mt_wide.size()));
+          mt_wide.insert(mt_wide.end(), rep.mt.begin(), rep.mt.end());
+          while (mt_wide.size() % 4) mt_wide.push_back(0);
+          wins.push_back(wd);
+        }
       }
       // the strings of one electron fewer and their one-orbital completions
       {
@@ -190,11 +193,13 @@ void build_tables(ffx_batch_s& b) {
         t.kt[cs] = b.upload_table(kt);
         t.nk[cs] = nk;
       }
-      t.win[cs] = b.upload_table(wins);
-      while (mt_all.size() % 4) mt_all.push_back(0);  // staged as int4 words
-      t.mt_all[cs] = b.upload_table(mt_all);
-      t.n_mt_all[cs] = (int)mt_all.size();
-      b.max_mt = std::max(b.max_mt, (int)mt_all.size());
+      t.win_real[cs] = b.upload_table(wins_real);
+      t.mt_real[cs] = (const int4*)b.upload_table(mt_real);
+      t.n_mt_real[cs] = (int)mt_real.size() / 8;
+      t.win[cs] = b.c64 ? b.upload_table(wins) : t.win_real[cs];
+      t.mt_all[cs] = b.c64 ? (const int4*)b.upload_table(mt_wide) : t.mt_real[cs];
+      t.n_mt_all[cs] = b.c64 ? (int)mt_wide.size() / 4 : t.n_mt_real[cs];
+      b.max_mt = std::max({b.max_mt, t.n_mt_all[cs], t.n_mt_real[cs]});
       // a segment task holds R rows; a transition-matrix task holds rdm_rows(R) rows of two states
       const size_t rows_held = std::max<size_t>((size_t)R, 2 * (size_t)rdm_rows(R));
       const size_t rb = (rows_held * (size_t)len * b.elem() + 15) & ~(size_t)15;

@@ -47,7 +47,7 @@ constexpr int kBatchMaxDynLds = 160 * 1024 - 256;
 
 struct BatchLds {
   char* rows;
-  int* mt;
+  int4* mt;
   double* wq;      // wq_rows x kBatchMaxOrb cross weights
   double* rowf;    // wq_rows complex row factors (or real row values)
   double* acc;     // 4 waves x 2 N^2 doubles (RDM) or 4 x 2N (diagonal gradients)
@@ -66,7 +66,7 @@ __host__ __device__ inline size_t seg_tab_doubles(int wq_rows) {
 }
 
 __host__ __device__ inline size_t batch_lds_kind(int kind, int lds_row_bytes, int max_mt, int wq_rows) {
-  const size_t tabs = (size_t)((max_mt + 3) & ~3) * 4 + seg_tab_doubles(wq_rows) * 8;
+  const size_t tabs = (size_t)max_mt * 16 + seg_tab_doubles(wq_rows) * 8;
   const size_t head = (size_t)lds_row_bytes + (size_t)kRedDoubles * 8;
   if (kind == BK_SEG) return head + tabs;
   if (kind >= 0) return head + (size_t)kAccDoubles * 8;
@@ -79,8 +79,8 @@ __device__ __forceinline__ BatchLds batch_lds_map(char* smem, const BatchDev& B,
   L.red = (double*)(smem + B.lds_row_bytes);
   char* p = (char*)(L.red + kRedDoubles);
   if (kind == BK_SEG || kind < 0) {
-    L.mt = (int*)p;
-    L.wq = (double*)(L.mt + ((B.max_mt + 3) & ~3));
+    L.mt = (int4*)p;
+    L.wq = (double*)(L.mt + B.max_mt);
     L.rowf = L.wq + B.wq_rows * kBatchMaxOrb;
     p = (char*)(L.rowf + 2 * B.wq_rows);
   }
@@ -481,9 +481,8 @@ __device__ __forceinline__ void seg_task(const BatchDev& B, const BPassDev& ps, 
   }
   for (int64_t x = nel + tid; x < (int64_t)RR * len; x += nthr) buf[x] = V{};
   {
-    // (the member-offset tables are a whole number of int4 words)
-    const int n4 = pick2(ty.n_mt_all, cs) >> 2;
-    const int4* m4 = (const int4*)pick2(ty.mt_all, cs);
+    const int n4 = REAL ? pick2(ty.n_mt_real, cs) : pick2(ty.n_mt_all, cs);
+    const int4* m4 = REAL ? pick2(ty.mt_real, cs) : pick2(ty.mt_all, cs);
     for (int i0 = tid; i0 < n4; i0 += 4 * nthr) {
       int4 q[4];
 #pragma unroll
@@ -492,7 +491,7 @@ __device__ __forceinline__ void seg_task(const BatchDev& B, const BPassDev& ps, 
       for (int u = 0; u < 4; ++u) keep(q[u]);
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (i0 + u * nthr < n4) ((int4*)L.mt)[i0 + u * nthr] = q[u];
+        if (i0 + u * nthr < n4) L.mt[i0 + u * nthr] = q[u];
     }
   }
   __syncthreads();
@@ -502,13 +501,14 @@ __device__ __forceinline__ void seg_task(const BatchDev& B, const BPassDev& ps, 
   double acc = 0.0;
   // each Givens stage's rotations and first class codes are requested a stage
   // ahead (as in the segment pass)
+  const SegWinDev* wins = REAL ? pick2(ty.win_real, cs) : pick2(ty.win, cs);
   RotLane<R> rl_next{nullptr};
   ChunkAhead fc_next{1, 1, -1, -1};
   auto fetch = [&](int si) {
     const StageDev st = uniform_load(ps.stages + si);
     if (st.type == ST_GIVENS) {
-      rl_next = fetch_rot_lane<R>(st.rots, st.nrot, lane);
-      fc_next = fetch_first_chunk(uniform_load(pick2(ty.win, cs) + st.a), wave, lane, nwaves);
+      rl_next = fetch_rot_lane<R>(st.rots);
+      fc_next = fetch_first_chunk(uniform_load(wins + st.a), wave, lane, nwaves);
     }
   };
   if (ps.n_stages > 0) fetch(0);
@@ -518,8 +518,8 @@ __device__ __forceinline__ void seg_task(const BatchDev& B, const BPassDev& ps, 
     const ChunkAhead fc = fc_next;
     if (si + 1 < ps.n_stages) fetch(si + 1);
     if (st.type == ST_GIVENS) {
-      const SegWinDev wt = uniform_load(pick2(ty.win, cs) + st.a);
-      givens_stage<W, REAL, R>(st.shape, buf, L.mt, wt, rl, st.nrot, wave, nwaves, lane, fc);
+      const SegWinDev wt = uniform_load(wins + st.a);
+      givens_stage<W, REAL, R>(st.shape, buf, (const char*)L.mt, wt, rl, st.nrot, wave, nwaves, lane, fc);
     } else {
       // per row: cross weights w_r[q] = sum_{p in row} C[p][q] and the row factor
       for (int i = tid; i < nr * N; i += nthr) {

@@ -39,6 +39,20 @@ struct V2T<float> {
 struct re128 {
   double x;
 };
+struct re64 {
+  float x;
+};
+// the part type of a complex type
+template <class R>
+struct P2T;
+template <>
+struct P2T<double> {
+  using type = re128;
+};
+template <>
+struct P2T<float> {
+  using type = re64;
+};
 
 // The scalar type of an element type, and whether the element is a single
 // plane part (real rotations only).
@@ -57,6 +71,11 @@ struct ElemT<zc64> {
 template <>
 struct ElemT<re128> {
   using R = double;
+  static constexpr bool plane = true;
+};
+template <>
+struct ElemT<re64> {
+  using R = float;
   static constexpr bool plane = true;
 };
 template <class V>
@@ -262,18 +281,84 @@ __device__ __forceinline__ void apply_rots(V* v, const RotDev* __restrict__ rots
   }
 }
 
-// The rotations of one stage, as the rotation loops see them: the stage's
-// rotation list g (a uniform pointer).  The parameters are read straight into
-// scalar registers (FP64 values for complex128 elements and row planes, their
-// FP32 copies for complex64), one rotation ahead of their use, so no vector
-// instruction moves them; the window position selects a scalar branch.
+// The rotations of one stage, as the rotation loops see them: a uniform
+// pointer to RotDev entries (generic stages) or to the packed parameters of a
+// stage shape.
 template <class R>
 struct RotLane {
-  const RotDev* g;
+  const void* g;
 };
 
 template <class T>
 __device__ __forceinline__ T uniform_load(const T* p);
+
+// Generic stages: rotation r's position and parameters, loaded one rotation
+// ahead; the position selects the code through a scalar branch.
+template <int W, int M, bool REAL, class V>
+__device__ __forceinline__ void apply_rots_lane(V* v, const RotLane<ER<V>>& rl, int nrot) {
+  using R = ER<V>;
+  if (nrot <= 0) return;
+  const RotDev* g = (const RotDev*)rl.g;
+  RotDev cur = uniform_load(g);
+  for (int r = 0; r < nrot; ++r) {
+    const RotDev nxt = uniform_load(g + (r + 1 < nrot ? r + 1 : r));
+    rot_dispatch<W, M, REAL, V>(cur.p, v, rot_q<REAL, R>(cur));
+    cur = nxt;
+  }
+}
+
+// The rotations of stage shape S, positions fixed at compile time: rotation I
+// acts on window position kShapeP[S][I].  The parameters stand back to back
+// (the shears (t, b) of real rotations or (c, sr, si) of complex ones, in the
+// element's precision, padded to whole groups) and arrive in scalar registers
+// in groups of rot_group rotations (48 or 64 bytes, one scalar load), the next
+// group requested before the current one is applied.  From the 72-byte RotDev
+// entries, one rotation ahead, a pass's parameters exceeded the 16 KB scalar
+// cache of two compute units, and every rotation waited on L2.
+template <int W, int M, bool REAL, class V, int S, int G>
+struct ShapeRots {
+  using R = ER<V>;
+  static constexpr int n = kShapeLen[S];
+  static constexpr int U = rot_group(REAL, sizeof(R) == 8);
+  struct Group {
+    RotQ<REAL, R> q[U];
+  };
+  static_assert(sizeof(Group) == U * (REAL ? 2 : 3) * sizeof(R), "packed parameters");
+  static __device__ __forceinline__ Group load(const void* p) { return uniform_load((const Group*)p + G); }
+  template <int I>
+  static __device__ __forceinline__ void one(V* v, const Group& cur) {
+    if constexpr (G * U + I < n) {
+      rot_one<W, M, kShapeP[S][G * U + I], REAL, V>(v, cur.q[I]);
+      // nothing of a later rotation is scheduled into this one, where it would
+      // only hold registers
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  template <int... I>
+  static __device__ __forceinline__ void all(V* v, const Group& cur, std::integer_sequence<int, I...>) {
+    (one<I>(v, cur), ...);
+  }
+  static __device__ __forceinline__ void apply(V* v, const void* p, const Group& cur) {
+    if constexpr ((G + 1) * U < n) {
+      using Next = ShapeRots<W, M, REAL, V, S, G + 1>;
+      const typename Next::Group nxt = Next::load(p);
+      __builtin_amdgcn_sched_barrier(0);
+      all(v, cur, std::make_integer_sequence<int, U>{});
+      Next::apply(v, p, nxt);
+    } else {
+      all(v, cur, std::make_integer_sequence<int, U>{});
+    }
+  }
+};
+
+// Complex rotations of complex64 rows keep the unpacked form: RotDev entries
+// here and 32-bit member offsets in lds_class32.  How the compiler contracts
+// the four products of such a rotation into fused multiply-adds follows from
+// the code around them, and in FP32 that moves results by 1e-7: with this code
+// they stay what they were.  (Real rotations are written as shears, whose
+// instructions are fixed, and FP64 results move by 1e-16.)
+template <bool REAL, class V>
+constexpr bool kWideClass = !REAL && std::is_same<V, zc64>::value;
 
 // a stage's rotation I, read with scalar loads: the shear parameters (t, b) of
 // a real rotation or (c, sr, si) of a complex one, in the element's precision
@@ -289,40 +374,21 @@ __device__ __forceinline__ RotQ<REAL, R> rot_params(const RotDev* g, int i) {
   return uniform_load((const RotQ<REAL, R>*)((const char*)(g + i) + off));
 }
 
-// Generic stages: rotation r's position and parameters, loaded one rotation
-// ahead; the position selects the code through a scalar branch.
-template <int W, int M, bool REAL, class V>
-__device__ __forceinline__ void apply_rots_lane(V* v, const RotLane<ER<V>>& rl, int nrot) {
-  using R = ER<V>;
-  if (nrot <= 0) return;
-  RotDev cur = uniform_load(rl.g);
-  for (int r = 0; r < nrot; ++r) {
-    const RotDev nxt = uniform_load(rl.g + (r + 1 < nrot ? r + 1 : r));
-    rot_dispatch<W, M, REAL, V>(cur.p, v, rot_q<REAL, R>(cur));
-    cur = nxt;
-  }
-}
-
-// The rotations of stage shape S, positions fixed at compile time: rotation I
-// acts on window position kShapeP[S][I]; its parameters arrive in scalar
-// registers, requested while rotation I - 1 is applied.
 template <int W, int M, bool REAL, class V, int S, int I>
 __device__ __forceinline__ RotQ<REAL, ER<V>> shape_rot(V* v, const RotDev* g, RotQ<REAL, ER<V>> cur) {
   using R = ER<V>;
   constexpr int n = kShapeLen[S];
   const RotQ<REAL, R> nxt = rot_params<REAL, R>(g, I + 1 < n ? I + 1 : I);
   rot_one<W, M, kShapeP[S][I], REAL, V>(v, cur);
-  // nothing of a later rotation is scheduled into this one, where it would
-  // only hold registers
   __builtin_amdgcn_sched_barrier(0);
   return nxt;
 }
 
 template <int W, int M, bool REAL, class V, int S, int... I>
-__device__ __forceinline__ void apply_shape(V* v, const RotLane<ER<V>>& rl, std::integer_sequence<int, I...>) {
+__device__ __forceinline__ void apply_shape(V* v, const RotDev* g, std::integer_sequence<int, I...>) {
   using R = ER<V>;
-  RotQ<REAL, R> q = rot_params<REAL, R>(rl.g, 0);
-  ((q = shape_rot<W, M, REAL, V, S, I>(v, rl.g, q)), ...);
+  RotQ<REAL, R> q = rot_params<REAL, R>(g, 0);
+  ((q = shape_rot<W, M, REAL, V, S, I>(v, g, q)), ...);
 }
 
 // Loads a small struct of uniform, read-only data (descriptor tables written
@@ -417,18 +483,83 @@ __device__ __forceinline__ double block_sum256(double v, double* sh) {
 // a class of an LDS-resident row: load its members into registers, apply the
 // stage's rotations, store them back (segment passes and batched tasks)
 // ---------------------------------------------------------------------------
-// member offsets come four at a time from 16-byte-aligned LDS tables
+// Member offsets are 16-bit element offsets, eight to a 16-byte word of the
+// LDS tables.  off16 gives the byte address of member K of a class: the half
+// word K of its table times the element stride ES, plus the class's byte
+// base, in one instruction.
+template <int ES, int H>
+__device__ __forceinline__ uint32_t off16(uint32_t w, uint32_t base) {
+  uint32_t r;
+  if constexpr (H == 0)
+    asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(r) : "v"(w), "n"(ES), "v"(base));
+  else
+    asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(r) : "v"(w), "n"(ES), "v"(base));
+  return r;
+}
 template <int K>
-__device__ __forceinline__ int pick(const int4& q) {
+__device__ __forceinline__ uint32_t pick(const uint4& q) {
+  if constexpr (((K >> 1) & 3) == 0) return q.x;
+  if constexpr (((K >> 1) & 3) == 1) return q.y;
+  if constexpr (((K >> 1) & 3) == 2) return q.z;
+  return q.w;
+}
+template <class V>
+__device__ __forceinline__ V& lds_at(char* row, uint32_t byte) {
+  return *(V*)(row + byte);
+}
+
+// A class: C(W, M) members, M = electrons in the window.  row: the LDS row;
+// base: the class's byte offset in it; moff: byte offset of its table.  The
+// table (three words for the widest class) stays in registers from the loads
+// to the stores.  (32-bit offsets, four to a word, took 5 + 5 word reads per
+// 20-member class, read again before the stores since 20 registers could not
+// be held: half as many LDS bytes as the members' own of a row plane.)
+template <int W, int M, bool REAL, class V, int S, int ES, bool HOLD, int... K>
+__device__ __forceinline__ void lds_class(char* __restrict__ row, uint32_t base, const char* mtl, uint32_t moff,
+                                          const RotLane<ER<V>>& rl, int nrot, std::integer_sequence<int, K...>) {
+  constexpr int C = sizeof...(K);
+  constexpr int Q = (C + 7) / 8;
+  V v[C];
+  uint4 q[Q];
+  using Rots = ShapeRots<W, M, REAL, V, S < 0 ? 0 : S, 0>;
+  typename Rots::Group first;
+  if constexpr (S >= 0) first = Rots::load(rl.g);
+  const uint4* m4 = (const uint4*)(mtl + moff);
+#pragma unroll
+  for (int i = 0; i < Q; ++i) q[i] = m4[i];
+  ((v[K] = lds_at<V>(row, off16<ES, K & 1>(pick<K>(q[K >> 3]), base))), ...);
+  if constexpr (S < 0)
+    apply_rots_lane<W, M, REAL, V>(v, rl, nrot);
+  else
+    Rots::apply(v, rl.g, first);
+  // nothing of the store-back is scheduled into the straight-line rotations,
+  // where it would only hold registers
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (HOLD) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) asm volatile("" : "+v"(q[i].x), "+v"(q[i].y), "+v"(q[i].z), "+v"(q[i].w));
+  } else {
+    uint32_t o = moff;
+    asm volatile("" : "+v"(o));
+#pragma unroll
+    for (int i = 0; i < Q; ++i) q[i] = ((const uint4*)(mtl + o))[i];
+  }
+  ((lds_at<V>(row, off16<ES, K & 1>(pick<K>(q[K >> 3]), base)) = v[K]), ...);
+}
+
+// The same from 32-bit offsets, four to a word (kWideClass): cbase in
+// elements, moff the index of the first offset.  They are read again before
+// the stores: hiding the table offset from the optimizer forces the reload.
+template <int K>
+__device__ __forceinline__ int pick4(const int4& q) {
   if constexpr ((K & 3) == 0) return q.x;
   if constexpr ((K & 3) == 1) return q.y;
   if constexpr ((K & 3) == 2) return q.z;
   return q.w;
 }
-
 template <int W, int M, bool REAL, class V, int S, int... K>
-__device__ __forceinline__ void lds_class(V* __restrict__ row, int cbase, const int* mtl, int moff,
-                                          const RotLane<ER<V>>& rl, int nrot, std::integer_sequence<int, K...>) {
+__device__ __forceinline__ void lds_class32(V* __restrict__ row, int cbase, const int* mtl, int moff,
+                                            const RotLane<ER<V>>& rl, int nrot, std::integer_sequence<int, K...>) {
   constexpr int C = sizeof...(K);
   constexpr int Q = (C + 3) / 4;
   V v[C];
@@ -437,17 +568,13 @@ __device__ __forceinline__ void lds_class(V* __restrict__ row, int cbase, const 
     const int4* m4 = (const int4*)(mtl + moff);
 #pragma unroll
     for (int i = 0; i < Q; ++i) q[i] = m4[i];
-    ((v[K] = row[cbase + pick<K>(q[K >> 2])]), ...);
+    ((v[K] = row[cbase + pick4<K>(q[K >> 2])]), ...);
   }
   if constexpr (S < 0)
     apply_rots_lane<W, M, REAL, V>(v, rl, nrot);
   else
-    apply_shape<W, M, REAL, V, S>(v, rl, std::make_integer_sequence<int, kShapeLen[S]>{});
-  // nothing of the store-back (the offset reloads in particular) is scheduled
-  // into the straight-line rotations, where it would only hold registers
+    apply_shape<W, M, REAL, V, S>(v, (const RotDev*)rl.g, std::make_integer_sequence<int, kShapeLen[S]>{});
   __builtin_amdgcn_sched_barrier(0);
-  // member offsets are re-read from LDS rather than held in registers across
-  // the rotations: hiding the table offset from the optimizer forces the reload
   {
     int o = moff;
     asm volatile("" : "+v"(o));
@@ -455,18 +582,30 @@ __device__ __forceinline__ void lds_class(V* __restrict__ row, int cbase, const 
     const int4* m4 = (const int4*)(mtl + o);
 #pragma unroll
     for (int i = 0; i < Q; ++i) q[i] = m4[i];
-    ((row[cbase + pick<K>(q[K >> 2])] = v[K]), ...);
+    ((row[cbase + pick4<K>(q[K >> 2])] = v[K]), ...);
   }
 }
 
 template <int W, bool REAL, class V, int S = -1, int M = 1>
-__device__ __forceinline__ void lds_m(int m, V* row, int cbase, const int* mtl, int moff, const RotLane<ER<V>>& rl,
-                                      int nrot) {
+__device__ __forceinline__ void lds_m32(int m, V* row, int cbase, const int* mtl, int moff,
+                                        const RotLane<ER<V>>& rl, int nrot) {
   if constexpr (M < W) {
     if (m == M)
-      lds_class<W, M, REAL, V, S>(row, cbase, mtl, moff, rl, nrot, std::make_integer_sequence<int, cbinom(W, M)>{});
+      lds_class32<W, M, REAL, V, S>(row, cbase, mtl, moff, rl, nrot, std::make_integer_sequence<int, cbinom(W, M)>{});
     else
-      lds_m<W, REAL, V, S, M + 1>(m, row, cbase, mtl, moff, rl, nrot);
+      lds_m32<W, REAL, V, S, M + 1>(m, row, cbase, mtl, moff, rl, nrot);
+  }
+}
+
+template <int W, bool REAL, class V, int S, int ES, bool HOLD, int M = 1>
+__device__ __forceinline__ void lds_m(int m, char* row, uint32_t base, const char* mtl, uint32_t moff,
+                                      const RotLane<ER<V>>& rl, int nrot) {
+  if constexpr (M < W) {
+    if (m == M)
+      lds_class<W, M, REAL, V, S, ES, HOLD>(row, base, mtl, moff, rl, nrot,
+                                            std::make_integer_sequence<int, cbinom(W, M)>{});
+    else
+      lds_m<W, REAL, V, S, ES, HOLD, M + 1>(m, row, base, mtl, moff, rl, nrot);
   }
 }
 
@@ -502,59 +641,71 @@ __device__ __forceinline__ ChunkAhead fetch_first_chunk(const SegWinDev& wt, int
   return f;
 }
 
-// The rotations of a stage, one per lane (lanes past nrot repeat the last
-// one and are never read), loaded without a lane-dependent branch so that the
-// load can be issued a stage ahead of its use.
+// a stage's rotation list
 template <class R>
-__device__ __forceinline__ RotLane<R> fetch_rot_lane(const RotDev* rots, int nrot, int lane) {
-  (void)nrot;
-  (void)lane;
+__device__ __forceinline__ RotLane<R> fetch_rot_lane(const void* rots) {
   // the same address in every lane; taken through readfirstlane so that the
   // compiler knows it and reads the parameters with scalar loads
   const uint64_t a = (uint64_t)(uintptr_t)rots;
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
-  return RotLane<R>{(const RotDev*)(uintptr_t)(((uint64_t)hi << 32) | lo)};
+  return RotLane<R>{(const void*)(uintptr_t)(((uint64_t)hi << 32) | lo)};
 }
 
-template <int W, bool REAL, class V, int S>
-__device__ __forceinline__ void givens_chunks(V* row, const int* mtl, const SegWinDev& wt, const RotLane<ER<V>>& rl,
-                                              int nrot, int wave, int nwaves, int lane, ChunkAhead first) {
-  constexpr bool two = !ElemT<V>::plane;  // the second chunk's code was requested ahead
+// TWO: the second chunk's code was requested ahead (see fetch_first_chunk).
+template <int W, bool REAL, class V, int S, int ES, bool TWO>
+__device__ __forceinline__ void givens_chunks(char* row, const char* mtl, const SegWinDev& wt,
+                                              const RotLane<ER<V>>& rl, int nrot, int wave, int nwaves, int lane,
+                                              ChunkAhead first) {
   for (int ch = wave, k = 0; ch < wt.n_chunks; ch += nwaves, ++k) {
     int m = first.m, code = first.code;
-    if (two && k == 1) {
+    if (TWO && k == 1) {
       m = first.m2;
       code = first.code2;
     } else if (k > 0) {
       m = uniform_load(wt.chunk_m + ch);
       code = wt.code[ch * 64 + lane];
     }
-    // a code holds the class base and the index of its member-offset table
-    if (code >= 0) lds_m<W, REAL, V, S>(m, row, code >> kCodeMoffBitsDev, mtl, code & ((1 << kCodeMoffBitsDev) - 1), rl, nrot);
+    if constexpr (kWideClass<REAL, V>) {
+      if (code >= 0)
+        lds_m32<W, REAL, V, S>(m, (V*)row, code >> kCodeMoffBitsDev, (const int*)mtl,
+                               code & ((1 << kCodeMoffBitsDev) - 1), rl, nrot);
+    } else {
+      // a code holds the class base, in elements (parts) V, and its table's index in 16-byte words
+      if (code >= 0)
+        lds_m<W, REAL, V, S, ES, TWO && ElemT<V>::plane>(
+            m, row, (uint32_t)(code >> kCodeMoffBitsDev) * (uint32_t)sizeof(V), mtl,
+            (uint32_t)(code & ((1 << kCodeMoffBitsDev) - 1)) << 4, rl, nrot);
+    }
   }
 }
 
-template <int W, bool REAL, class V, int S = 0>
-__device__ __forceinline__ void givens_stage_v(int shape, V* row, const int* mtl, const SegWinDev& wt,
+// ES: distance in bytes between consecutive elements of the row (2 sizeof(V)
+// when V is a part of the complex elements)
+template <int W, bool REAL, class V, int ES, bool TWO, int S = 0>
+__device__ __forceinline__ void givens_stage_v(int shape, char* row, const char* mtl, const SegWinDev& wt,
                                                const RotLane<ER<V>>& rl, int nrot, int wave, int nwaves, int lane,
                                                ChunkAhead first) {
   if constexpr (W == kShapeW && S < kNumShapes) {
     if (shape == S)
-      givens_chunks<W, REAL, V, S>(row, mtl, wt, rl, nrot, wave, nwaves, lane, first);
+      givens_chunks<W, REAL, V, S, ES, TWO>(row, mtl, wt, rl, nrot, wave, nwaves, lane, first);
     else
-      givens_stage_v<W, REAL, V, S + 1>(shape, row, mtl, wt, rl, nrot, wave, nwaves, lane, first);
+      givens_stage_v<W, REAL, V, ES, TWO, S + 1>(shape, row, mtl, wt, rl, nrot, wave, nwaves, lane, first);
   } else {
-    givens_chunks<W, REAL, V, -1>(row, mtl, wt, rl, nrot, wave, nwaves, lane, first);
+    givens_chunks<W, REAL, V, -1, ES, TWO>(row, mtl, wt, rl, nrot, wave, nwaves, lane, first);
   }
 }
 
-// the same on rows of complex amplitudes of scalar type R
-template <int W, bool REAL, class R>
-__device__ __forceinline__ void givens_stage(int shape, typename V2T<R>::type* row, const int* mtl,
+// The same on rows of complex amplitudes of scalar type R.  SPLIT (real
+// rotations): the two parts of an amplitude in neighbouring lanes, from class
+// tables of 32 classes to a chunk (split_seg_window).
+template <int W, bool REAL, class R, bool SPLIT = false>
+__device__ __forceinline__ void givens_stage(int shape, typename V2T<R>::type* row, const char* mtl,
                                              const SegWinDev& wt, const RotLane<R>& rl, int nrot, int wave,
                                              int nwaves, int lane, ChunkAhead first) {
-  givens_stage_v<W, REAL, typename V2T<R>::type>(shape, row, mtl, wt, rl, nrot, wave, nwaves, lane, first);
+  using V = typename std::conditional<SPLIT, typename P2T<R>::type, typename V2T<R>::type>::type;
+  givens_stage_v<W, REAL, V, 2 * (int)sizeof(R), true>(shape, (char*)row, mtl, wt, rl, nrot, wave, nwaves, lane,
+                                                       first);
 }
 
 __device__ __forceinline__ int parity(uint32_t x) { return __builtin_popcount(x) & 1; }

@@ -72,9 +72,9 @@ struct DiagJobDev {
   uint32_t sign;
 };
 
-// Register window of the Givens passes: W = 6 for both precisions (complex64
-// also has a W = 7 instantiation, which holds 12 waves instead of 16 and
-// measured slower; complex128 at W = 6 fills 143 registers, so 12 waves).
+// Register window of the Givens passes: W = 6 for both precisions (W = 7 at
+// complex64 holds 12 waves instead of 16 and measured slower; complex128 at W =
+// 6 fills 143 registers, so 12 waves).
 inline int max_window(bool) { return 6; }
 
 // c128 = complex double state, c64 = complex float state.
@@ -240,6 +240,11 @@ constexpr int kShapeP[kNumShapes][kShapeMaxLen] = {
     {1, 2, 3, 4, 0, 1, 2, 3, 0, 1, 2, 0, 1, 0},
 };
 
+// Rotations per group of a shape's packed parameters: real rotations hold (t,
+// b) in doubles or floats, complex ones (c, sr, si) in doubles; groups of 64 or
+// 48 bytes.
+constexpr int rot_group(bool real, bool dbl) { return real ? (dbl ? 4 : 8) : 2; }
+
 // f(row, col) = A[row] + B[col] + sum_{p in row, q in col} C[p * norb + q]
 //   ST_PHASE : x *= (-1)^{|row & sign_row|} exp(i (scale (A[row] + cross) + sum_{p in row} drow[p]))
 //                   * colf[col]
@@ -258,7 +263,10 @@ struct StageDev {
   // ST_PHASE: column orbitals whose occupation parity flips the sign (a
   // deferred sign layer of the column spin that needs no column table)
   uint32_t sign_col;
-  const RotDev* rots;
+  // ST_GIVENS: the packed parameters of its shape, whole groups of rot_group
+  // rotations in the launch's precision, or RotDev entries (shape -1, and
+  // complex rotations of complex64 states)
+  const void* rots;
   double scale;
   const double* A;
   const double* B;
@@ -269,17 +277,17 @@ struct StageDev {
 
 // Class tables of one register window inside one segment.  Chunk ch holds 64
 // lanes; code[ch * 64 + lane] = (cbase << kCodeMoffBitsDev) | moff for the
-// lane's class (-1 for padding), where member k of the class sits at cbase +
-// mt_all[moff + k] (moff = mt_off + mt[m * nl1 + l] for m electrons in the
-// window and l below it, folded in on the host).  Chunks are listed in order
-// of decreasing work; classes with an empty or full window are omitted.
+// lane's class (-1 for padding): its members sit at cbase + the 16-bit offsets
+// that start at 16-byte word moff of the segment's mt_all (one table per
+// number of electrons in the window and below it); for complex rotations of
+// complex64 rows the offsets are 32-bit and moff counts them singly.  Chunks
+// are listed in order of decreasing work; classes with an empty or full window
+// are omitted.
 constexpr int kCodeMoffBitsDev = 14;
 struct SegWinDev {
   const int* code;
   const int* chunk_m;
-  int mt_off;  // start of this window's offsets inside the segment's mt_all
   int n_chunks;
-  int nl1;
   int pad;
 };
 
@@ -289,8 +297,8 @@ struct SegWinDev {
 struct SegDev {
   int off, len;
   const SegWinDev* win;
-  const int* mt_all;  // member offsets of every window, staged into LDS once per block
-  int n_mt_all;
+  const int4* mt_all;  // member offsets of every window, staged into LDS once per block
+  int n_mt_all;        // 16-byte words
   // crossing rotation on (wt - 1, wt), the orbital pair that straddles the
   // segment window: it pairs the strings [cross_lo, cross_lo + cross_cnt) of
   // this segment elementwise with cross_cnt strings from column cross_peer on
@@ -316,7 +324,8 @@ struct SegPassDev {
   const StageDev* stages;
   double* partials;
   int lds_row_bytes;  // byte offset of the scratch area after the row segment
-  int max_mt;         // ints reserved in LDS for the member offsets of all windows
+  int max_mt;         // 16-byte words reserved in LDS for the member offsets of all windows
+  int direct;         // diagonal stages evaluate the cross term per element, without byte tables
   // when set, the crossing rotation (cross_c, cross_sr + i cross_si) is applied
   // as the segment is loaded, reading the partner strings from src (which the
   // pass must not overwrite: src != dst)
@@ -365,8 +374,12 @@ struct BTypeDev {
   // rows_per_task[cs] rows; window tables replicated over those rows
   int rows_per_task[2];
   const SegWinDev* win[2];
-  const int* mt_all[2];
-  int n_mt_all[2];
+  const int4* mt_all[2];
+  int n_mt_all[2];  // 16-byte words
+  // the same for real rotations (complex64: 16-bit member offsets)
+  int n_mt_real[2];
+  const SegWinDev* win_real[2];
+  const int4* mt_real[2];
   // per string spin s, for the transition one-body matrices: the strings K of
   // n_s - 1 electrons, nk[s] of them, and for each K and orbital o < 16:
   // kt[s][16 K + o] = 2 rank(K + o) + parity(K below o) if o < norb and o is
@@ -427,7 +440,7 @@ struct BatchDev {
   unsigned int* done;     // per instance: finished tasks
   unsigned int* abort;    // set when a wait exceeds its bound
   int lds_row_bytes;      // LDS bytes reserved for the rows of one task
-  int max_mt;             // ints reserved for member-offset tables
+  int max_mt;             // 16-byte words reserved for member-offset tables
   int wq_rows;            // rows reserved for the cross weights and row factors (the most rows of a task)
   int pad2;
 };
@@ -450,11 +463,12 @@ int batch_coop_blocks_per_cu(bool c64, size_t lds);
 hipError_t batch_launch_coop(bool c64, const BatchDev& b, const int* level_start, int n_levels,
                              unsigned int* level_ctr, int blocks, size_t lds, hipStream_t s);
 
-size_t seg_pass_lds(bool c64, int max_len, int max_mt);
-// block size a segment pass launches with for a requested size (the kernel's
-// register budget caps it)
-int seg_pass_threads(bool c64, int W, int requested);
-// blocks = n_rows * n_seg; partials (if any stage reduces) get one entry per block
+// (max_mt in 16-byte words)
+size_t seg_pass_lds(bool c64, int norb, int max_len, int max_mt, bool direct);
+// the most threads a segment pass's registers leave room for on a compute unit, in one block or several
+int seg_pass_max_threads(bool c64, int W, bool split);
+// blocks = n_rows * n_seg; partials (if any stage reduces) get one entry per block.  Real rotations at W = 6 take the
+// class tables of split_seg_window.
 void seg_pass(bool c64, bool real, int W, const SegPassDev& p, int block_threads, size_t lds_bytes,
               hipStream_t stream);
 // in-place transpose of a square n x n state

@@ -349,6 +349,32 @@ WindowTable build_window_table(const std::vector<uint64_t>& strs, int norb, int 
   return t;
 }
 
+namespace {
+
+// chunks of 64 lanes in order of decreasing work from the lane codes of each m
+void chunks_from_codes(const std::map<int, std::vector<int>>& by_m, int w, SegWindowTable& o) {
+  struct Chunk {
+    int m;
+    double cost;
+    std::vector<int> codes;
+  };
+  std::vector<Chunk> chunks;
+  for (const auto& kv : by_m) {
+    const double cost = (double)binom(w, kv.first) * (2.0 + (double)binom(w - 2, kv.first - 1));
+    for (size_t i = 0; i < kv.second.size(); i += 64)
+      chunks.push_back(Chunk{kv.first, cost,
+                             std::vector<int>(kv.second.begin() + i,
+                                              kv.second.begin() + std::min(i + 64, kv.second.size()))});
+  }
+  std::stable_sort(chunks.begin(), chunks.end(), [](const Chunk& x, const Chunk& y) { return x.cost > y.cost; });
+  for (const Chunk& ch : chunks) {
+    o.chunk_m.push_back(ch.m);
+    for (int j = 0; j < 64; ++j) o.code.push_back(j < (int)ch.codes.size() ? ch.codes[j] : -1);
+  }
+}
+
+}  // namespace
+
 SegWindowTable build_seg_window(const std::vector<uint64_t>& seg, int wt, int a, int w, int group) {
   SegWindowTable t;
   const uint64_t low_mask = (wt >= 64) ? ~0ull : ((1ull << wt) - 1);
@@ -438,26 +464,7 @@ SegWindowTable build_seg_window(const std::vector<uint64_t>& seg, int wt, int a,
       }
     }
   }
-  struct Chunk {
-    int m;
-    double cost;
-    std::vector<int> codes;
-  };
-  std::vector<Chunk> chunks;
-  for (auto& kv : by_m) {
-    const int m = kv.first;
-    const double cost = (double)binom(w, m) * (2.0 + (double)binom(w - 2, m - 1));
-    for (size_t i = 0; i < kv.second.size(); i += 64) {
-      Chunk ch{m, cost, {}};
-      for (size_t j = i; j < std::min(i + 64, kv.second.size()); ++j) ch.codes.push_back(kv.second[j]);
-      chunks.push_back(std::move(ch));
-    }
-  }
-  std::stable_sort(chunks.begin(), chunks.end(), [](const Chunk& x, const Chunk& y) { return x.cost > y.cost; });
-  for (auto& ch : chunks) {
-    t.chunk_m.push_back(ch.m);
-    for (int j = 0; j < 64; ++j) t.code.push_back(j < (int)ch.codes.size() ? ch.codes[j] : -1);
-  }
+  chunks_from_codes(by_m, w, t);
   return t;
 }
 
@@ -572,6 +579,45 @@ std::vector<int> pack_class_codes(const SegWindowTable& t, int mt_off) {
   return out;
 }
 
+SegWindowTable compact_members(const SegWindowTable& t, int w, std::vector<uint16_t>& out) {
+  SegWindowTable o;
+  o.nl1 = t.nl1;
+  o.code = t.code;
+  o.chunk_m = t.chunk_m;
+  o.mt.assign((size_t)(w + 1) * t.nl1, 0);
+  std::vector<char> used((size_t)(w + 1) * t.nl1, 0);
+  for (size_t ch = 0; ch < t.chunk_m.size(); ++ch)
+    for (int j = 0; j < 64; ++j)
+      if (t.code[ch * 64 + j] >= 0) used[(size_t)t.chunk_m[ch] * t.nl1 + (t.code[ch * 64 + j] & 31)] = 1;
+  for (int m = 1; m < w; ++m)
+    for (int l = 0; l < t.nl1; ++l) {
+      if (!used[(size_t)m * t.nl1 + l]) continue;
+      o.mt[(size_t)m * t.nl1 + l] = (int)(out.size() / 8);
+      const int* src = t.mt.data() + t.mt[(size_t)m * t.nl1 + l];
+      for (int k = 0; k < (int)binom(w, m); ++k) {
+        if (src[k] < 0 || src[k] > 65535) throw Error(FFX_EUNSUPPORTED, "member offset exceeds 16 bits");
+        out.push_back((uint16_t)src[k]);
+      }
+      while (out.size() % 8) out.push_back(0);
+    }
+  return o;
+}
+
+SegWindowTable split_seg_window(const SegWindowTable& t, int w) {
+  SegWindowTable o;
+  o.nl1 = t.nl1;
+  o.mt = t.mt;
+  std::map<int, std::vector<int>> by_m;
+  for (size_t ch = 0; ch < t.chunk_m.size(); ++ch)
+    for (int j = 0; j < 64; ++j) {
+      const int c = t.code[ch * 64 + j];
+      if (c < 0) continue;
+      for (int part = 0; part < 2; ++part) by_m[t.chunk_m[ch]].push_back(((2 * (c >> 5) + part) << 5) | (c & 31));
+    }
+  chunks_from_codes(by_m, w, o);
+  return o;
+}
+
 SegWindowTable replicate_seg_window(const SegWindowTable& t, int w, int R, int row_len) {
   SegWindowTable o;
   o.nl1 = t.nl1;
@@ -587,26 +633,7 @@ SegWindowTable replicate_seg_window(const SegWindowTable& t, int w, int R, int r
         by_m[t.chunk_m[ch]].push_back((int)((cbase << 5) | (c & 31)));
       }
   for (auto& kv : by_m) std::sort(kv.second.begin(), kv.second.end());
-  struct Chunk {
-    int m;
-    double cost;
-    std::vector<int> codes;
-  };
-  std::vector<Chunk> chunks;
-  for (auto& kv : by_m) {
-    const int m = kv.first;
-    const double cost = (double)binom(w, m) * (2.0 + (double)binom(w - 2, m - 1));
-    for (size_t i = 0; i < kv.second.size(); i += 64) {
-      Chunk ch{m, cost, {}};
-      for (size_t j = i; j < std::min(i + 64, kv.second.size()); ++j) ch.codes.push_back(kv.second[j]);
-      chunks.push_back(std::move(ch));
-    }
-  }
-  std::stable_sort(chunks.begin(), chunks.end(), [](const Chunk& x, const Chunk& y) { return x.cost > y.cost; });
-  for (auto& ch : chunks) {
-    o.chunk_m.push_back(ch.m);
-    for (int j = 0; j < 64; ++j) o.code.push_back(j < (int)ch.codes.size() ? ch.codes[j] : -1);
-  }
+  chunks_from_codes(by_m, w, o);
   return o;
 }
 

@@ -129,10 +129,23 @@ SegWindowTable replicate_seg_window(const SegWindowTable& t, int w, int R, int r
 // chunk of m electrons in the window, (cbase << kCodeMoffBits) | moff with moff
 // = mt_off + mt[m * nl1 + l], the index of the class's member-offset table in
 // the segment's LDS table block (mt_off: where this window's tables start in
-// it), so a lane finds its offsets without first looking up that index; -1
-// stays -1.  Error if cbase or moff does not fit its field.
+// it; 0 for compacted tables, whose mt holds that index already), so a lane
+// finds its offsets without first looking up that index; -1 stays -1.  Error if cbase or moff does not fit its field.
 constexpr int kCodeMoffBits = 14;
 std::vector<int> pack_class_codes(const SegWindowTable& t, int mt_off);
+
+// The member-offset tables of a window as the device keeps them: for every
+// (m, l) that a class of the table uses (0 < m < w), the C(w, m) offsets as
+// 16-bit values, padded to whole 16-byte words and appended to out.  Returns
+// the table with mt[m * nl1 + l] = the index, in 16-byte words of out, of that
+// (m, l)'s offsets (pack_class_codes then takes mt_off = 0).
+SegWindowTable compact_members(const SegWindowTable& t, int w, std::vector<uint16_t>& out);
+
+// The class table for real rotations with the real and imaginary parts of an
+// amplitude in neighbouring lanes: lanes 2 j and 2 j + 1 of a chunk hold the
+// two parts of one class, with bases counted in parts (2 cbase and 2 cbase +
+// 1), so a chunk holds 32 classes.
+SegWindowTable split_seg_window(const SegWindowTable& t, int w);
 
 // Reorders the chunks of a segment-pass window table for a block of nwaves
 // waves, which take chunks wave, wave + nwaves, ...: the chunks are spread over

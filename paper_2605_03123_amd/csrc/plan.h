@@ -44,7 +44,13 @@ struct ffx_plan_s {
     size_t lds = 0;
     int threads = 256;
     bool cross = false;  // rotations on (wt - 1, wt) can be applied at segment load
+    bool direct = false;  // diagonal stages without byte tables
     ffx::dev::SegDev* d_segs = nullptr;
+    // class tables for real rotations, with their block size and LDS
+    ffx::dev::SegDev* d_real = nullptr;
+    int threads_real = 256;
+    int max_mt_real = 0;
+    size_t lds_real = 0;
   } seg[2];
   // whole rows as two planes (complex128 rows that exceed LDS but whose real
   // parts fit): one segment per row, for visits whose rotations are all real;

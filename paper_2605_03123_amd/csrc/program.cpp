@@ -223,6 +223,31 @@ int stage_shape(const std::vector<dev::RotDev>& rots, int w) {
   return -1;
 }
 
+// a Givens stage's rotations as its kernel reads them: the packed parameters
+// of a stage shape in the launch's kind and precision, or RotDev entries
+const void* put_rots(Upload& up, int shape, const std::vector<dev::RotDev>& rots, bool real, bool c64) {
+  if (shape < 0 || (c64 && !real)) return up.put(rots.data(), rots.size());
+  const size_t group = (size_t)dev::rot_group(real, !c64), w = real ? 2 : 3;
+  const size_t n = (rots.size() + group - 1) / group * group;
+  std::vector<double> d(c64 ? 0 : n * w, 0.0);
+  std::vector<float> f(c64 ? n * w : 0, 0.0f);
+  for (size_t i = 0; i < rots.size(); ++i) {
+    const dev::RotDev& r = rots[i];
+    if (c64) {
+      f[2 * i] = r.ft;
+      f[2 * i + 1] = r.fb;
+    } else if (real) {
+      d[2 * i] = r.t;
+      d[2 * i + 1] = r.b;
+    } else {
+      d[3 * i] = r.c;
+      d[3 * i + 1] = r.sr;
+      d[3 * i + 2] = r.si;
+    }
+  }
+  return c64 ? (const void*)up.put(f.data(), f.size()) : (const void*)up.put(d.data(), d.size());
+}
+
 }  // namespace
 
 Compiled compile_program(ffx_plan_s& P, Upload& up, const Program& prog, int final_mode, hipStream_t s) {
@@ -371,6 +396,7 @@ Compiled compile_program(ffx_plan_s& P, Upload& up, const Program& prog, int fin
     const int ncol = P.n[colspin()];
     const double pairs_per_row = (double)binom(N - 2, ncol - 1);
     std::vector<dev::StageDev> stages;
+    std::vector<std::vector<dev::RotDev>> stage_rots;  // per stage (empty: a diagonal stage)
     Launch cur{};
     cur.kind = Launch::SEG;
     cur.layout = layout;
@@ -378,10 +404,14 @@ Compiled compile_program(ffx_plan_s& P, Upload& up, const Program& prog, int fin
     bool any = false;
     auto flush_seg = [&](bool force) {
       if (stages.empty() && !force && !cur.cross) return;
+      // (here, since one complex rotation makes the whole launch complex)
+      for (size_t k = 0; k < stages.size(); ++k)
+        if (stages[k].type == dev::ST_GIVENS) stages[k].rots = put_rots(up, stages[k].shape, stage_rots[k], cur.real, P.c64);
       cur.stages = stages.empty() ? nullptr : up.put(stages.data(), stages.size());
       cur.n_stages = (int)stages.size();
       c.launches.push_back(cur);
       stages.clear();
+      stage_rots.clear();
       cur = Launch{};
       cur.kind = Launch::SEG;
       cur.layout = layout;
@@ -390,6 +420,7 @@ Compiled compile_program(ffx_plan_s& P, Upload& up, const Program& prog, int fin
     for (const Item& it : visit) {
       if (it.kind == 1) {
         stages.push_back(it.st);
+        stage_rots.push_back({});
         if (it.st.type == dev::ST_REDUCE) cur.reduce = true;
         any = true;
         continue;
@@ -424,8 +455,8 @@ Compiled compile_program(ffx_plan_s& P, Upload& up, const Program& prog, int fin
           st.a = step.a;
           st.nrot = (int)buf.size();
           st.shape = stage_shape(buf, ss.Wseg);
-          st.rots = up.put(buf.data(), buf.size());
           stages.push_back(st);
+          stage_rots.push_back(std::move(buf));
           cur.real = cur.real && d.real;
           cur.valu_slots += slots;
           cur.rot_sides += step.idx.size() / K;
@@ -667,12 +698,14 @@ void execute_program(ffx_plan_s& P, const Compiled& c, const void* src, void* wo
       p.row_masks = P.d_masks[L.layout == 0 ? 0 : 1];
       p.col_masks = P.d_masks[cs];
       p.n_seg = ss.n_seg;
-      p.segs = ss.d_segs;
+      const bool real_set = !L.planes && L.real;
+      p.segs = real_set ? ss.d_real : ss.d_segs;
+      p.direct = ss.direct ? 1 : 0;
       p.n_stages = L.n_stages;
       p.stages = L.stages;
       p.partials = L.reduce ? P.partials : nullptr;
       p.lds_row_bytes = (int)(((size_t)ss.max_len * (L.planes ? 8 : P.elem()) + 15) & ~(size_t)15);
-      p.max_mt = ss.max_mt;
+      p.max_mt = real_set ? ss.max_mt_real : ss.max_mt;
       if (L.cross) {
         p.cross = 1;
         p.cross_c = L.cross_rot.c;
@@ -699,7 +732,8 @@ void execute_program(ffx_plan_s& P, const Compiled& c, const void* src, void* wo
       if (L.planes)
         dev::seg_pass_planes(ss.Wseg, ss.threads, p, ss.lds, s);
       else
-        dev::seg_pass(P.c64, L.real, ss.Wseg, p, ss.threads, ss.lds, s);
+        dev::seg_pass(P.c64, L.real, ss.Wseg, p, real_set ? ss.threads_real : ss.threads,
+                      real_set ? ss.lds_real : ss.lds, s);
       check_launch();
       if (L.reduce) {
         dev::sum_partials(P.partials, (int)(rows * ss.n_seg), L.reduce_out, s);

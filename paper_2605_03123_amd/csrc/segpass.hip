@@ -30,12 +30,12 @@
 namespace ffx {
 namespace dev {
 
-// 12 waves per block (3 per SIMD): the widest register windows (W = 7 at
-// complex64, W = 6 at complex128) fit in the 168 registers this leaves a lane;
-// narrower windows fit in 128 registers and run 16 waves
-template <int W, class R>
+// 12 waves per block (3 per SIMD): the widest complex128 window (W = 6) fits in
+// the 168 registers this leaves a lane; complex64, narrower windows, and lanes
+// that hold one part of each member fit in 128 registers and run 16 waves
+template <int W, class R, bool SPLIT = false>
 constexpr int seg_threads() {
-  return (sizeof(R) == 4 ? W <= 6 : W <= 5) ? 1024 : 768;
+  return SPLIT || sizeof(R) == 4 || W < kShapeW ? 1024 : 768;
 }
 
 // The rotation on the orbital pair that straddles the segment window, for
@@ -116,11 +116,14 @@ __device__ __forceinline__ void cross_apply(typename V2T<R>::type* own, const ty
 
 // Row-dependent part of a diagonal stage, computed by the whole block before
 // the stage touches any element: the cross weights w[q] = sum_{p in row} C[p][q]
-// (the row's masked C is staged in the table area, one load per thread, all in
-// flight at once, then summed over p in a fixed order), the row value A[r], the
-// row's phase factor (phase stages; with a cross term it is folded into the
-// first byte table), and the byte tables of the cross term: complex factors for
-// phase stages, real sums otherwise.  Ends with a block barrier.
+// (a column of C per thread, all its loads in flight at once, summed over p in
+// a fixed order), the row value A[r], the row's phase factor (phase stages;
+// with a cross term and byte tables it is folded into the first table), and
+// the byte tables of the cross term: complex factors for phase stages, real
+// sums otherwise.  With `direct` (segments shorter than the tables) the stage
+// takes the sum of the weights, and a phase's sine and cosine, per element:
+// a table of 256 entries per byte costs as many of them as 256 elements.
+// Ends with a block barrier.
 struct DiagRow {
   double arow;
   zc128 rowf;
@@ -129,22 +132,23 @@ struct DiagRow {
 
 __device__ __forceinline__ DiagRow diag_stage_tables(const StageDev& st, const SegPassDev& P, int64_t r,
                                                      uint32_t rmask, zc128* ez, double* wq, int tid, int nthr,
-                                                     int nbytes) {
+                                                     int nbytes, bool direct) {
   double* tab = (double*)ez;
   DiagRow dr;
   dr.cross = st.C != nullptr;
-  const int nn = P.norb * P.norb;
-  if (dr.cross) {
-    for (int i = tid; i < nn; i += nthr) tab[i] = ((rmask >> (i / P.norb)) & 1) ? st.C[i] : 0.0;
-    __syncthreads();
-  }
   if (tid < P.norb) {
     double w = 0.0;
     if (dr.cross)
-      for (int p = 0; p < P.norb; ++p) w += tab[p * P.norb + tid];
+      for (int p0 = 0; p0 < P.norb; p0 += 16) {
+        double c[16];
+#pragma unroll
+        for (int p = 0; p < 16; ++p) c[p] = st.C[min(p0 + p, P.norb - 1) * P.norb + tid];
+#pragma unroll
+        for (int p = 0; p < 16; ++p)
+          if (p0 + p < P.norb && ((rmask >> (p0 + p)) & 1)) w += c[p];
+      }
     wq[tid] = w;
   }
-  __syncthreads();
   dr.arow = st.A ? st.A[r] : 0.0;
   dr.rowf = zc128{1.0, 0.0};
   if (st.type == ST_PHASE) {
@@ -158,7 +162,8 @@ __device__ __forceinline__ DiagRow diag_stage_tables(const StageDev& st, const S
       dr.rowf.y = -dr.rowf.y;
     }
   }
-  if (dr.cross) {
+  __syncthreads();
+  if (dr.cross && !direct) {
     for (int i = tid; i < nbytes * 256; i += nthr) {
       const int k = i >> 8, b = i & 255;
       double v = 0.0;
@@ -171,21 +176,46 @@ __device__ __forceinline__ DiagRow diag_stage_tables(const StageDev& st, const S
         tab[i] = v;
       }
     }
+    __syncthreads();
   }
-  __syncthreads();
   return dr;
 }
 
-template <int W, bool REAL, class R>
-__global__ __launch_bounds__((seg_threads<W, R>())) void k_seg_pass(SegPassDev P) {
+// LDS after the row: the byte tables (none for direct evaluation), the member
+// offsets of every window, the cross weights and the reduction scratch
+struct SegLds {
+  zc128* ez;   // nbytes x 256 complex byte factors (or real byte sums)
+  int4* mt;
+  double* wq;  // 32 cross weights
+  double* red;
+};
+__device__ __forceinline__ SegLds seg_lds_map(char* smem, const SegPassDev& P, int nbytes) {
+  SegLds L;
+  L.ez = (zc128*)(smem + P.lds_row_bytes);
+  L.mt = (int4*)(L.ez + (P.direct ? 0 : nbytes * 256));
+  L.wq = (double*)(L.mt + P.max_mt);
+  L.red = L.wq + 32;
+  return L;
+}
+
+// SPLIT (real rotations at W = 6): neighbouring lanes take the two parts of the
+// members of one class (split_seg_window).  A lane then holds C(W, m) parts
+// instead of twice as many, so a compute unit runs 16 waves of 20-member windows
+// instead of 12, a stage's longest chain is half as long, and a row's few
+// classes fill twice the lanes.  A 14-orbital DF step took 13.2 ms without it
+// and 8.4 ms with it, a 10-orbital one 1.50 and 1.37 ms, a 16-orbital complex64
+// one (whose rows fill a block either way) 52.8 and 52.4 ms.
+template <int W, bool REAL, class R, bool SPLIT>
+__global__ __launch_bounds__((seg_threads<W, R, SPLIT>())) void k_seg_pass(SegPassDev P) {
   using V = typename V2T<R>::type;
   extern __shared__ __align__(16) char smem[];
   V* row = (V*)smem;
-  zc128* ez = (zc128*)(smem + P.lds_row_bytes);      // 4 x 256 complex byte factors
-  double* tab = (double*)ez;                          // (or 4 x 256 real byte sums)
-  int* mtl = (int*)(ez + 4 * 256);                    // member offsets of one window
-  double* wq = (double*)(mtl + ((P.max_mt + 3) & ~3)); // 32 cross weights
-  double* red = wq + 32;                               // block reduction scratch
+  const int nbytes = (P.norb + 7) >> 3;
+  const SegLds L = seg_lds_map(smem, P, nbytes);
+  zc128* ez = L.ez;
+  double* tab = (double*)ez;
+  double* wq = L.wq;
+  double* red = L.red;
 
   int si;
   int64_t r;
@@ -215,8 +245,8 @@ __global__ __launch_bounds__((seg_threads<W, R>())) void k_seg_pass(SegPassDev P
                            : (const V*)P.src + r * P.row_len + sg.cross_peer;
   V xt[kCrossU];
   // (the member-offset table of every window is a whole number of int4 words)
-  stage_segment<sizeof(V) == 8 ? 13 : 9, 2>(row, src, sg.len, (int4*)mtl, (const int4*)sg.mt_all,
-                                            sg.n_mt_all >> 2, peer, xrot ? sg.cross_cnt : 0, xt, tid, nthr, stride);
+  stage_segment<sizeof(V) == 8 ? 13 : 9, 2>(row, src, sg.len, L.mt, sg.mt_all, sg.n_mt_all, peer,
+                                            xrot ? sg.cross_cnt : 0, xt, tid, nthr, stride);
   __syncthreads();
   if (xrot) {
     cross_apply<R>(row + sg.cross_lo, xt, peer, sg.cross_cnt, sg.cross_role, P.cross_c, P.cross_sr, P.cross_si,
@@ -226,7 +256,6 @@ __global__ __launch_bounds__((seg_threads<W, R>())) void k_seg_pass(SegPassDev P
 
   const uint32_t rmask = P.row_masks[r];
   const uint32_t* cmask = P.col_masks + sg.off;
-  const int nbytes = (P.norb + 7) >> 3;
   double acc = 0.0;
 
   // the vector-memory data of a Givens stage (its rotations, the wave's first
@@ -237,7 +266,7 @@ __global__ __launch_bounds__((seg_threads<W, R>())) void k_seg_pass(SegPassDev P
   auto fetch = [&](int s) {
     const StageDev st = uniform_load(P.stages + s);
     if (st.type == ST_GIVENS) {
-      rl_next = fetch_rot_lane<R>(st.rots, st.nrot, lane);
+      rl_next = fetch_rot_lane<R>(st.rots);
       fc_next = fetch_first_chunk(uniform_load(sg.win + st.a), wave, lane, nwaves);
     }
   };
@@ -249,9 +278,9 @@ __global__ __launch_bounds__((seg_threads<W, R>())) void k_seg_pass(SegPassDev P
     if (s + 1 < P.n_stages) fetch(s + 1);
     if (st.type == ST_GIVENS) {
       const SegWinDev wt = uniform_load(sg.win + st.a);
-      givens_stage<W, REAL, R>(st.shape, row, mtl, wt, rl, st.nrot, wave, nwaves, lane, fc);
+      givens_stage<W, REAL, R, SPLIT>(st.shape, row, (const char*)L.mt, wt, rl, st.nrot, wave, nwaves, lane, fc);
     } else {
-      const DiagRow dr = diag_stage_tables(st, P, r, rmask, ez, wq, tid, nthr, nbytes);
+      const DiagRow dr = diag_stage_tables(st, P, r, rmask, ez, wq, tid, nthr, nbytes, P.direct);
       const bool cross = dr.cross;
       const double arow = dr.arow;
       zc128 rowf = dr.rowf;
@@ -259,7 +288,39 @@ __global__ __launch_bounds__((seg_threads<W, R>())) void k_seg_pass(SegPassDev P
       // usual block sizes): their column masks and tables are all requested
       // before the first is used
       constexpr int U = sizeof(V) == 8 ? 10 : 9;
-      if (st.type == ST_PHASE) {
+      if (cross && P.direct) {
+        // (a loop of its own, not unrolled: one copy of the sine and cosine)
+        const zc128* colf = st.colf ? (const zc128*)st.colf + sg.off : nullptr;
+        const double* Bs = st.B ? st.B + sg.off : nullptr;
+#pragma unroll 1
+        for (int e = tid; e < sg.len; e += nthr) {
+          const uint32_t cm = cmask[e];
+          double v = 0.0;
+          for (uint32_t x = cm; x; x &= x - 1) v += wq[__builtin_ctz(x)];
+          V y = row[e];
+          if (st.type == ST_PHASE) {
+            zc128 f = zmul(rowf, phase_factor<double>(st.scale * v));
+            if (colf) f = zmul(f, colf[e]);
+            if (parity(cm & st.sign_col)) {
+              f.x = -f.x;
+              f.y = -f.y;
+            }
+            V o;
+            o.x = (R)((double)y.x * f.x - (double)y.y * f.y);
+            o.y = (R)((double)y.x * f.y + (double)y.y * f.x);
+            row[e] = o;
+          } else {
+            const double f = arow + (Bs ? Bs[e] : 0.0) + v;
+            if (st.type == ST_SCALE) {
+              y.x = (R)(f * (double)y.x);
+              y.y = (R)(f * (double)y.y);
+              row[e] = y;
+            } else {
+              acc += f * ((double)y.x * (double)y.x + (double)y.y * (double)y.y);
+            }
+          }
+        }
+      } else if (st.type == ST_PHASE) {
         if (cross) rowf = zc128{1.0, 0.0};
         const zc128* colf = st.colf ? (const zc128*)st.colf + sg.off : nullptr;
         const uint32_t sgn = st.sign_col;
@@ -402,10 +463,10 @@ int seg_pass_plane_max_len(int threads) { return threads * (threads == 512 ? pla
 // Givens stages [s0, s1) of a plane pass on the LDS plane; each stage's
 // rotations and the wave's first class codes are requested one stage ahead.
 template <int W>
-__device__ __forceinline__ void plane_givens_run(const SegPassDev& P, const SegDev& sg, re128* pl, const int* mtl,
+__device__ __forceinline__ void plane_givens_run(const SegPassDev& P, const SegDev& sg, re128* pl, const char* mtl,
                                                  int s0, int s1, int wave, int nwaves, int lane) {
   StageDev st = uniform_load(P.stages + s0);
-  RotLane<double> rl_next = fetch_rot_lane<double>(st.rots, st.nrot, lane);
+  RotLane<double> rl_next = fetch_rot_lane<double>(st.rots);
   ChunkAhead fc_next = fetch_first_chunk<false>(uniform_load(sg.win + st.a), wave, lane, nwaves);
   for (int s = s0; s < s1; ++s) {
     st = uniform_load(P.stages + s);
@@ -413,11 +474,11 @@ __device__ __forceinline__ void plane_givens_run(const SegPassDev& P, const SegD
     const ChunkAhead fc = fc_next;
     if (s + 1 < s1) {
       const StageDev nx = uniform_load(P.stages + s + 1);
-      rl_next = fetch_rot_lane<double>(nx.rots, nx.nrot, lane);
+      rl_next = fetch_rot_lane<double>(nx.rots);
       fc_next = fetch_first_chunk<false>(uniform_load(sg.win + nx.a), wave, lane, nwaves);
     }
     const SegWinDev wt = uniform_load(sg.win + st.a);
-    givens_stage_v<W, true, re128>(st.shape, pl, mtl, wt, rl, st.nrot, wave, nwaves, lane, fc);
+    givens_stage_v<W, true, re128, 8, false>(st.shape, (char*)pl, mtl, wt, rl, st.nrot, wave, nwaves, lane, fc);
     __syncthreads();
   }
 }
@@ -427,12 +488,14 @@ template <int W, int NT, bool SEGS>
 __global__ __launch_bounds__(NT) void k_seg_pass_planes(SegPassDev P) {
   constexpr int kPlaneRegs = plane_regs<NT>();
   extern __shared__ __align__(16) char smem[];
-  re128* pl = (re128*)smem;                            // the LDS plane
-  zc128* ez = (zc128*)(smem + P.lds_row_bytes);        // 4 x 256 complex byte factors
-  double* tab = (double*)ez;                           // (or 4 x 256 real byte sums)
-  int* mtl = (int*)(ez + 4 * 256);                     // member offsets of every window
-  double* wq = (double*)(mtl + ((P.max_mt + 3) & ~3)); // 32 cross weights
-  double* red = wq + 32;                               // block reduction scratch
+  re128* pl = (re128*)smem;  // the LDS plane
+  const int nbytes = (P.norb + 7) >> 3;
+  const SegLds L = seg_lds_map(smem, P, nbytes);
+  zc128* ez = L.ez;
+  double* tab = (double*)ez;
+  const char* mtl = (const char*)L.mt;
+  double* wq = L.wq;
+  double* red = L.red;
 
   // block -> (row, segment) as in the segment pass
   int si = 0;
@@ -484,13 +547,12 @@ __global__ __launch_bounds__(NT) void k_seg_pass_planes(SegPassDev P) {
       rp[k] = t[k].y;
     }
   }
-  for (int e = tid; e < (sg.n_mt_all >> 2); e += nthr) ((int4*)mtl)[e] = ((const int4*)sg.mt_all)[e];
+  for (int e = tid; e < sg.n_mt_all; e += nthr) L.mt[e] = sg.mt_all[e];
   __syncthreads();
   bool lds_re = true;  // the LDS plane holds the real parts (the same in every thread)
 
   const uint32_t rmask = P.row_masks[r];
   const uint32_t* cmask = P.col_masks + off;
-  const int nbytes = (P.norb + 7) >> 3;
   double acc = 0.0;
   int s = 0;
   while (s < P.n_stages) {
@@ -516,7 +578,7 @@ __global__ __launch_bounds__(NT) void k_seg_pass_planes(SegPassDev P) {
       s = s1;
       continue;
     }
-    const DiagRow dr = diag_stage_tables(st, P, r, rmask, ez, wq, tid, nthr, nbytes);
+    const DiagRow dr = diag_stage_tables(st, P, r, rmask, ez, wq, tid, nthr, nbytes, false);
     const bool cross = dr.cross;
     if (st.type == ST_PHASE) {
       const zc128 rowf = cross ? zc128{1.0, 0.0} : dr.rowf;
@@ -634,28 +696,28 @@ void seg_pass_planes(int W, int threads, const SegPassDev& p, size_t lds, hipStr
     planes_w<512>(W, p, lds, s);
 }
 
-size_t seg_pass_lds(bool c64, int max_len, int max_mt) {
+size_t seg_pass_lds(bool c64, int norb, int max_len, int max_mt, bool direct) {
   size_t row = (size_t)max_len * (c64 ? 8 : 16);
   row = (row + 15) & ~(size_t)15;
-  return row + 4 * 256 * sizeof(zc128) + (size_t)((max_mt + 3) & ~3) * sizeof(int) + (32 + 16) * sizeof(double);
+  const size_t tabs = direct ? 0 : (size_t)((norb + 7) / 8) * 256 * sizeof(zc128);
+  return row + tabs + (size_t)max_mt * 16 + (32 + 16) * sizeof(double);
 }
 
-int seg_pass_threads(bool c64, int W, int requested) {
-  const int cap = c64 ? (W <= 6 ? seg_threads<6, float>() : seg_threads<7, float>())
-                      : (W <= 5 ? seg_threads<5, double>() : seg_threads<6, double>());
-  return std::min(requested, cap);
+int seg_pass_max_threads(bool c64, int W, bool split) {
+  if (split) return seg_threads<kShapeW, double, true>();
+  return c64 ? seg_threads<kShapeW, float>() : (W < kShapeW ? seg_threads<kShapeW - 1, double>() : seg_threads<kShapeW, double>());
 }
 
-template <int W, bool REAL, class R>
+template <int W, bool REAL, class R, bool SPLIT = false>
 static void launch_seg(const SegPassDev& p, int threads, size_t lds, hipStream_t s) {
-  auto k = k_seg_pass<W, REAL, R>;
+  auto k = k_seg_pass<W, REAL, R, SPLIT>;
   static bool attr_set = false;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     attr_set = true;
   }
   const int64_t blocks = p.xcd_rows > 0 ? 8 * p.xcd_rows * p.n_seg : p.n_rows * p.n_seg;
-  hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(std::min(threads, seg_threads<W, R>())), lds, s, p);
+  hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(std::min(threads, seg_threads<W, R, SPLIT>())), lds, s, p);
 }
 
 template <bool REAL, class R>
@@ -666,10 +728,7 @@ static void launch_seg_w(int W, const SegPassDev& p, int threads, size_t lds, hi
     case 3: launch_seg<3, REAL, R>(p, threads, lds, s); break;
     case 4: launch_seg<4, REAL, R>(p, threads, lds, s); break;
     case 5: launch_seg<5, REAL, R>(p, threads, lds, s); break;
-    case 6: launch_seg<6, REAL, R>(p, threads, lds, s); break;
-    case 7:
-      if constexpr (sizeof(R) == 4) launch_seg<7, REAL, R>(p, threads, lds, s);
-      break;
+    case kShapeW: launch_seg<kShapeW, REAL, R, REAL>(p, threads, lds, s); break;
     default: break;
   }
 }

@@ -45,3 +45,21 @@ def test_string_tables_of_a_diagonal_gate(ffx, norb, nelec, dtype):
     ref = og.apply_diag_coulomb_evolution(_ref(v), J[0], 0.7, norb, nelec, J_ab=Jab, J_bb=J[1])
     ref = og.apply_num_op_sum_evolution(ref, lam, 0.3, norb, nelec, lam_b=lam_b)
     assert np.max(np.abs(_ref(out) - ref)) <= TOL[dtype]
+
+
+# rows of few classes and of many, rows just below and above the length from which a diagonal stage tabulates its
+# cross term (256 entries per byte of orbitals), blocks alone on a compute unit and sharing one
+@pytest.mark.parametrize("norb,nelec", [(6, (3, 2)), (7, (1, 6)), (8, (4, 4)), (9, (3, 5)), (11, (5, 2)), (12, (4, 5)),
+                                        (13, (6, 1))])
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+@pytest.mark.parametrize("real", [True, False])
+def test_rotations_around_a_phase(ffx, norb, nelec, dtype, real):
+    r = synth.rng([43, norb, nelec[0], nelec[1], int(real)])
+    v = _state(r, norb, nelec, dtype)
+    U = (synth.random_orthogonal if real else synth.random_unitary)(r, norb)
+    J = synth.random_symmetric(r, norb, 0.4)
+    out = ffx.apply_diag_coulomb_evolution(v, J, 0.9, norb, nelec, orbital_rotation=U)
+    ref = og.apply_orbital_rotation(_ref(v), U.conj().T, norb, nelec)
+    ref = og.apply_diag_coulomb_evolution(ref, J, 0.9, norb, nelec)
+    ref = og.apply_orbital_rotation(ref, U, norb, nelec)
+    assert np.max(np.abs(_ref(out) - ref)) <= TOL[dtype]

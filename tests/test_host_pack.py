@@ -1,0 +1,23 @@
+"""The device forms of the segment class tables (16-bit member offsets, parts of an amplitude in neighbouring
+lanes) against the tables they are made from, on the CPU (tests/host_pack_check.cpp)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_2605_03123_amd", "csrc")
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_device_class_tables_reach_the_same_members(tmp_path):
+    exe = tmp_path / "pack_check"
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-D_GLIBCXX_ASSERTIONS", f"-I{os.path.join(ROOT, 'include')}",
+           f"-I{CSRC}", os.path.join(CSRC, "host.cpp"), os.path.join(HERE, "host_pack_check.cpp"), "-o", str(exe)]
+    build = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert build.returncode == 0, build.stderr[-4000:]
+    run = subprocess.run([str(exe)], capture_output=True, text=True, timeout=600)
+    assert run.returncode == 0, (run.stdout[-2000:], run.stderr[-2000:])
+    assert "pack checks passed" in run.stdout
