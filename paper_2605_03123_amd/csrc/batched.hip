@@ -726,6 +726,10 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch_kind(BatchDev B, int p0
     else
       hi = mid - 1;
   }
+  // the index is the same in every lane; through readfirstlane the compiler
+  // knows it, and the descriptors, stage lists and rotation parameters reached
+  // from it come through scalar loads
+  lo = __builtin_amdgcn_readfirstlane(lo);
   const BPassDev ps = uniform_load(B.passes + lo);
   const BTypeDev ty = uniform_load(B.types + ps.type);
   const int task = (int)(t - ps.first);
@@ -776,6 +780,7 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch_coop(BatchDev B, const 
           else
             hi = mid - 1;
         }
+        lo = __builtin_amdgcn_readfirstlane(lo);  // (as in k_batch_kind)
         const BPassDev ps = uniform_load(B.passes + lo);
         const BTypeDev ty = uniform_load(B.types + ps.type);
         const int task = (int)(t - ps.first);

@@ -157,7 +157,7 @@ __device__ __forceinline__ V cmul(V a, V b) {
   return r;
 }
 
-// d <- a * d + b and d <- a * b + d, written into d's own register: with the
+// d <- a * d + b, written into d's own register: with the
 // result tied to the input, the member registers never move across the
 // rotation loop.  a is a rotation parameter, the same in every lane: it is
 // read from scalar registers (one scalar operand per instruction, within the
@@ -168,13 +168,6 @@ __device__ __forceinline__ void fma_ip(float& d, float a, float b) {
 __device__ __forceinline__ void fma_ip(double& d, double a, double b) {
   asm("v_fma_f64 %0, %1, %0, %2" : "+v"(d) : "s"(a), "v"(b));
 }
-__device__ __forceinline__ void fma_acc(float& d, float a, float b) {
-  asm("v_fma_f32 %0, %1, %2, %0" : "+v"(d) : "s"(a), "v"(b));
-}
-__device__ __forceinline__ void fma_acc(double& d, double a, double b) {
-  asm("v_fma_f64 %0, %1, %2, %0" : "+v"(d) : "s"(a), "v"(b));
-}
-
 // The parameters of one rotation as the rotation code takes them.  Complex
 // sine: (c, sr, si).  Real sine: the rotation [[c, s], [-s, c]] with c >= 0
 // (every cosine of a decomposition is) is the product of three shears,
@@ -195,11 +188,15 @@ template <bool REAL, class R>
 using RotQ = typename std::conditional<REAL, RotShear<R>, RotCplx<R>>::type;
 
 // one component of a member pair under the three shears
+// (plain fused multiply-adds: written as asm, the compiler kept them apart by
+// wait states, one for every six)
+__device__ __forceinline__ double fma1(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma1(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 template <class R>
 __device__ __forceinline__ void shear3(R& x, R& y, R t, R b) {
-  fma_acc(x, t, y);
-  fma_acc(y, b, x);
-  fma_acc(x, t, y);
+  x = fma1(t, y, x);
+  y = fma1(b, x, y);
+  x = fma1(t, y, x);
 }
 
 // x' = c x + s y, y' = -conj(s) x + c y on one member pair (A, B)
@@ -503,20 +500,45 @@ __device__ __forceinline__ uint32_t pick(const uint4& q) {
   if constexpr (((K >> 1) & 3) == 2) return q.z;
   return q.w;
 }
-template <class V>
-__device__ __forceinline__ V& lds_at(char* row, uint32_t byte) {
-  return *(V*)(row + byte);
+// LDS by byte address (through a pointer into the row, every access added the
+// row's address, zero, to its own)
+#define FFX_LDS __attribute__((address_space(3)))
+typedef double lds_d2 __attribute__((ext_vector_type(2)));
+typedef float lds_f2 __attribute__((ext_vector_type(2)));
+typedef uint32_t lds_u4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(uintptr_t)(const FFX_LDS char*)p; }
+__device__ __forceinline__ uint4 lds_word(uint32_t a) {
+  const lds_u4 t = *(const FFX_LDS lds_u4*)(uintptr_t)a;
+  return uint4{t.x, t.y, t.z, t.w};
 }
+__device__ __forceinline__ void lds_get(re128& v, uint32_t a) { v.x = *(const FFX_LDS double*)(uintptr_t)a; }
+__device__ __forceinline__ void lds_get(re64& v, uint32_t a) { v.x = *(const FFX_LDS float*)(uintptr_t)a; }
+__device__ __forceinline__ void lds_get(zc128& v, uint32_t a) {
+  const lds_d2 t = *(const FFX_LDS lds_d2*)(uintptr_t)a;
+  v.x = t.x;
+  v.y = t.y;
+}
+__device__ __forceinline__ void lds_get(zc64& v, uint32_t a) {
+  const lds_f2 t = *(const FFX_LDS lds_f2*)(uintptr_t)a;
+  v.x = t.x;
+  v.y = t.y;
+}
+__device__ __forceinline__ void lds_put(const re128& v, uint32_t a) { *(FFX_LDS double*)(uintptr_t)a = v.x; }
+__device__ __forceinline__ void lds_put(const re64& v, uint32_t a) { *(FFX_LDS float*)(uintptr_t)a = v.x; }
+__device__ __forceinline__ void lds_put(const zc128& v, uint32_t a) {
+  *(FFX_LDS lds_d2*)(uintptr_t)a = lds_d2{v.x, v.y};
+}
+__device__ __forceinline__ void lds_put(const zc64& v, uint32_t a) { *(FFX_LDS lds_f2*)(uintptr_t)a = lds_f2{v.x, v.y}; }
 
-// A class: C(W, M) members, M = electrons in the window.  row: the LDS row;
-// base: the class's byte offset in it; moff: byte offset of its table.  The
+// A class: C(W, M) members, M = electrons in the window.  base, moff: the LDS
+// byte addresses that its members count from and of its offset table.  The
 // table (three words for the widest class) stays in registers from the loads
 // to the stores.  (32-bit offsets, four to a word, took 5 + 5 word reads per
 // 20-member class, read again before the stores since 20 registers could not
 // be held: half as many LDS bytes as the members' own of a row plane.)
 template <int W, int M, bool REAL, class V, int S, int ES, bool HOLD, int... K>
-__device__ __forceinline__ void lds_class(char* __restrict__ row, uint32_t base, const char* mtl, uint32_t moff,
-                                          const RotLane<ER<V>>& rl, int nrot, std::integer_sequence<int, K...>) {
+__device__ __forceinline__ void lds_class(uint32_t base, uint32_t moff, const RotLane<ER<V>>& rl, int nrot,
+                                          std::integer_sequence<int, K...>) {
   constexpr int C = sizeof...(K);
   constexpr int Q = (C + 7) / 8;
   V v[C];
@@ -524,10 +546,9 @@ __device__ __forceinline__ void lds_class(char* __restrict__ row, uint32_t base,
   using Rots = ShapeRots<W, M, REAL, V, S < 0 ? 0 : S, 0>;
   typename Rots::Group first;
   if constexpr (S >= 0) first = Rots::load(rl.g);
-  const uint4* m4 = (const uint4*)(mtl + moff);
 #pragma unroll
-  for (int i = 0; i < Q; ++i) q[i] = m4[i];
-  ((v[K] = lds_at<V>(row, off16<ES, K & 1>(pick<K>(q[K >> 3]), base))), ...);
+  for (int i = 0; i < Q; ++i) q[i] = lds_word(moff + 16 * i);
+  (lds_get(v[K], off16<ES, K & 1>(pick<K>(q[K >> 3]), base)), ...);
   if constexpr (S < 0)
     apply_rots_lane<W, M, REAL, V>(v, rl, nrot);
   else
@@ -542,9 +563,9 @@ __device__ __forceinline__ void lds_class(char* __restrict__ row, uint32_t base,
     uint32_t o = moff;
     asm volatile("" : "+v"(o));
 #pragma unroll
-    for (int i = 0; i < Q; ++i) q[i] = ((const uint4*)(mtl + o))[i];
+    for (int i = 0; i < Q; ++i) q[i] = lds_word(o + 16 * i);
   }
-  ((lds_at<V>(row, off16<ES, K & 1>(pick<K>(q[K >> 3]), base)) = v[K]), ...);
+  (lds_put(v[K], off16<ES, K & 1>(pick<K>(q[K >> 3]), base)), ...);
 }
 
 // The same from 32-bit offsets, four to a word (kWideClass): cbase in
@@ -598,14 +619,12 @@ __device__ __forceinline__ void lds_m32(int m, V* row, int cbase, const int* mtl
 }
 
 template <int W, bool REAL, class V, int S, int ES, bool HOLD, int M = 1>
-__device__ __forceinline__ void lds_m(int m, char* row, uint32_t base, const char* mtl, uint32_t moff,
-                                      const RotLane<ER<V>>& rl, int nrot) {
+__device__ __forceinline__ void lds_m(int m, uint32_t base, uint32_t moff, const RotLane<ER<V>>& rl, int nrot) {
   if constexpr (M < W) {
     if (m == M)
-      lds_class<W, M, REAL, V, S, ES, HOLD>(row, base, mtl, moff, rl, nrot,
-                                            std::make_integer_sequence<int, cbinom(W, M)>{});
+      lds_class<W, M, REAL, V, S, ES, HOLD>(base, moff, rl, nrot, std::make_integer_sequence<int, cbinom(W, M)>{});
     else
-      lds_m<W, REAL, V, S, ES, HOLD, M + 1>(m, row, base, mtl, moff, rl, nrot);
+      lds_m<W, REAL, V, S, ES, HOLD, M + 1>(m, base, moff, rl, nrot);
   }
 }
 
@@ -674,8 +693,8 @@ __device__ __forceinline__ void givens_chunks(char* row, const char* mtl, const 
       // a code holds the class base, in elements (parts) V, and its table's index in 16-byte words
       if (code >= 0)
         lds_m<W, REAL, V, S, ES, TWO && ElemT<V>::plane>(
-            m, row, (uint32_t)(code >> kCodeMoffBitsDev) * (uint32_t)sizeof(V), mtl,
-            (uint32_t)(code & ((1 << kCodeMoffBitsDev) - 1)) << 4, rl, nrot);
+            m, lds_addr(row) + (uint32_t)(code >> kCodeMoffBitsDev) * (uint32_t)sizeof(V),
+            lds_addr(mtl) + ((uint32_t)(code & ((1 << kCodeMoffBitsDev) - 1)) << 4), rl, nrot);
     }
   }
 }
