@@ -181,6 +181,17 @@ __device__ __forceinline__ DiagRow diag_stage_tables(const StageDev& st, const S
   return dr;
 }
 
+// The launch parameters, read again from the kernel's argument segment: kept
+// across the stages they, and values computed from them, would hold (or spill)
+// scalar registers that the rotation parameters need.
+__device__ __forceinline__ SegPassDev reload_params() {
+  using carg = const __attribute__((address_space(4))) char;
+  carg* kp = (carg*)__builtin_amdgcn_kernarg_segment_ptr();
+  uint64_t a = (uint64_t)kp;
+  asm volatile("" : "+s"(a));
+  return uniform_load((const SegPassDev*)a);
+}
+
 // LDS after the row: the byte tables (none for direct evaluation), the member
 // offsets of every window, the cross weights and the reduction scratch
 struct SegLds {
@@ -210,12 +221,7 @@ __global__ __launch_bounds__((seg_threads<W, R, SPLIT>())) void k_seg_pass(SegPa
   using V = typename V2T<R>::type;
   extern __shared__ __align__(16) char smem[];
   V* row = (V*)smem;
-  const int nbytes = (P.norb + 7) >> 3;
-  const SegLds L = seg_lds_map(smem, P, nbytes);
-  zc128* ez = L.ez;
-  double* tab = (double*)ez;
-  double* wq = L.wq;
-  double* red = L.red;
+  const SegLds L = seg_lds_map(smem, P, (P.norb + 7) >> 3);
 
   int si;
   int64_t r;
@@ -228,7 +234,6 @@ __global__ __launch_bounds__((seg_threads<W, R, SPLIT>())) void k_seg_pass(SegPa
     si = (int)(blockIdx.x % P.n_seg);
     r = blockIdx.x / P.n_seg;
   }
-  const int64_t blk = r * P.n_seg + si;
   const SegDev sg = uniform_load(P.segs + si);
   const int nthr = blockDim.x;
   const int tid = threadIdx.x;
@@ -254,8 +259,6 @@ __global__ __launch_bounds__((seg_threads<W, R, SPLIT>())) void k_seg_pass(SegPa
     __syncthreads();
   }
 
-  const uint32_t rmask = P.row_masks[r];
-  const uint32_t* cmask = P.col_masks + sg.off;
   double acc = 0.0;
 
   // the vector-memory data of a Givens stage (its rotations, the wave's first
@@ -280,6 +283,14 @@ __global__ __launch_bounds__((seg_threads<W, R, SPLIT>())) void k_seg_pass(SegPa
       const SegWinDev wt = uniform_load(sg.win + st.a);
       givens_stage<W, REAL, R, SPLIT>(st.shape, row, (const char*)L.mt, wt, rl, st.nrot, wave, nwaves, lane, fc);
     } else {
+      const SegPassDev P = reload_params();
+      const int nbytes = (P.norb + 7) >> 3;
+      const SegLds L = seg_lds_map(smem, P, nbytes);
+      zc128* ez = L.ez;
+      double* tab = (double*)ez;
+      double* wq = L.wq;
+      const uint32_t rmask = P.row_masks[r];
+      const uint32_t* cmask = P.col_masks + sg.off;
       const DiagRow dr = diag_stage_tables(st, P, r, rmask, ez, wq, tid, nthr, nbytes, P.direct);
       const bool cross = dr.cross;
       const double arow = dr.arow;
@@ -403,12 +414,13 @@ __global__ __launch_bounds__((seg_threads<W, R, SPLIT>())) void k_seg_pass(SegPa
     __syncthreads();
   }
 
-  if (P.mode != SEG_NONE) {
+  const SegPassDev Q = reload_params();
+  if (Q.mode != SEG_NONE) {
     // row r of this layout, or (scatter) column r of the other one
-    const int64_t ostride = P.scatter ? P.n_rows : 1;
-    V* dst = P.scatter ? (V*)P.dst + r + (int64_t)sg.off * P.n_rows : (V*)P.dst + r * P.row_len + sg.off;
-    if (P.mode == SEG_STORE) {
-      if (P.scatter)
+    const int64_t ostride = Q.scatter ? Q.n_rows : 1;
+    V* dst = Q.scatter ? (V*)Q.dst + r + (int64_t)sg.off * Q.n_rows : (V*)Q.dst + r * Q.row_len + sg.off;
+    if (Q.mode == SEG_STORE) {
+      if (Q.scatter)
         stage_out_strided<128 / sizeof(V)>(dst, row, sg.len, ostride, tid, nthr);
       else
         stage_in<128 / sizeof(V)>(dst, row, sg.len, tid, nthr);
@@ -421,15 +433,16 @@ __global__ __launch_bounds__((seg_threads<W, R, SPLIT>())) void k_seg_pass(SegPa
       }
     }
   }
-  if (P.partials) {
+  if (Q.partials) {
     // fixed-order block reduction: wave sums, then thread 0 adds them in order
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+    double* red = seg_lds_map(smem, Q, (Q.norb + 7) >> 3).red;
     if (lane == 0) red[wave] = acc;
     __syncthreads();
     if (tid == 0) {
       double t = 0.0;
       for (int i = 0; i < nwaves; ++i) t += red[i];
-      P.partials[blk] = t;
+      Q.partials[r * Q.n_seg + si] = t;
     }
   }
 }
@@ -503,13 +516,8 @@ __global__ __launch_bounds__(NT) void k_seg_pass_planes(SegPassDev P) {
   constexpr int kPlaneRegs = plane_regs<NT>();
   extern __shared__ __align__(16) char smem[];
   re128* pl = (re128*)smem;  // the LDS plane
-  const int nbytes = (P.norb + 7) >> 3;
-  const SegLds L = seg_lds_map(smem, P, nbytes);
-  zc128* ez = L.ez;
-  double* tab = (double*)ez;
+  const SegLds L = seg_lds_map(smem, P, (P.norb + 7) >> 3);
   const char* mtl = (const char*)L.mt;
-  double* wq = L.wq;
-  double* red = L.red;
 
   // block -> (row, segment) as in the segment pass
   int si = 0;
@@ -532,7 +540,6 @@ __global__ __launch_bounds__(NT) void k_seg_pass_planes(SegPassDev P) {
       r = blockIdx.x;
     }
   }
-  const int64_t blk = SEGS ? r * P.n_seg + si : r;
   const SegDev sg = uniform_load(P.segs + si);
   const int off = SEGS ? sg.off : 0;  // the segment's first column
   const int len = sg.len;
@@ -566,8 +573,6 @@ __global__ __launch_bounds__(NT) void k_seg_pass_planes(SegPassDev P) {
   __syncthreads();
   bool lds_re = true;  // the LDS plane holds the real parts (the same in every thread)
 
-  const uint32_t rmask = P.row_masks[r];
-  const uint32_t* cmask = P.col_masks + off;
   double acc = 0.0;
   int s = 0;
   while (s < P.n_stages) {
@@ -575,24 +580,37 @@ __global__ __launch_bounds__(NT) void k_seg_pass_planes(SegPassDev P) {
     if (st.type == ST_GIVENS) {
       int s1 = s + 1;
       while (s1 < P.n_stages && uniform_load(P.stages + s1).type == ST_GIVENS) ++s1;
-      plane_givens_run<W>(P, sg, pl, mtl, s, s1, wave, nwaves, lane);
-      // swap the planes: the register plane into LDS and back
+      // the run on one plane, a swap of the planes (the register plane into LDS
+      // and back), the run on the other; a loop, so that the stages' code is
+      // there once
+#pragma unroll 1
+      for (int half = 0;; ++half) {
+        plane_givens_run<W>(P, sg, pl, mtl, s, s1, wave, nwaves, lane);
+        if (half) break;
 #pragma unroll
-      for (int k = 0; k < kPlaneRegs; ++k) {
-        int e = tid + k * nthr;
-        asm volatile("" : "+v"(e));  // recomputed here: hoisted, 26 such offsets would stay live across stages
-        if (e < len) {
-          const double x = pl[e].x;
-          pl[e].x = rp[k];
-          rp[k] = x;
+        for (int k = 0; k < kPlaneRegs; ++k) {
+          int e = tid + k * nthr;
+          asm volatile("" : "+v"(e));  // recomputed here: hoisted, 26 such offsets would stay live across stages
+          if (e < len) {
+            const double x = pl[e].x;
+            pl[e].x = rp[k];
+            rp[k] = x;
+          }
         }
+        __syncthreads();
       }
-      __syncthreads();
       lds_re = !lds_re;
-      plane_givens_run<W>(P, sg, pl, mtl, s, s1, wave, nwaves, lane);
       s = s1;
       continue;
     }
+    const SegPassDev P = reload_params();
+    const int nbytes = (P.norb + 7) >> 3;
+    const SegLds L = seg_lds_map(smem, P, nbytes);
+    zc128* ez = L.ez;
+    double* tab = (double*)ez;
+    double* wq = L.wq;
+    const uint32_t rmask = P.row_masks[r];
+    const uint32_t* cmask = P.col_masks + off;
     const DiagRow dr = diag_stage_tables(st, P, r, rmask, ez, wq, tid, nthr, nbytes, false);
     const bool cross = dr.cross;
     if (st.type == ST_PHASE) {
@@ -644,17 +662,18 @@ __global__ __launch_bounds__(NT) void k_seg_pass_planes(SegPassDev P) {
     ++s;
   }
 
-  if (P.mode != SEG_NONE) {
+  const SegPassDev Q = reload_params();
+  if (Q.mode != SEG_NONE) {
     // row r of this layout, or (scatter) column r of the other one
-    const int64_t ostride = P.scatter ? P.n_rows : 1;
-    zc128* dst = P.scatter ? (zc128*)P.dst + r + (int64_t)off * P.n_rows : (zc128*)P.dst + r * P.row_len + off;
+    const int64_t ostride = Q.scatter ? Q.n_rows : 1;
+    zc128* dst = Q.scatter ? (zc128*)Q.dst + r + (int64_t)off * Q.n_rows : (zc128*)Q.dst + r * Q.row_len + off;
 #pragma unroll
     for (int k = 0; k < kPlaneRegs; ++k) {
       const int e = tid + k * nthr;
       if (e < len) {
         const double a = pl[e].x, q = rp[k];
         zc128 v = lds_re ? zc128{a, q} : zc128{q, a};
-        if (P.mode == SEG_ACCUM) {
+        if (Q.mode == SEG_ACCUM) {
           const zc128 o = dst[e * ostride];
           v.x += o.x;
           v.y += o.y;
@@ -663,15 +682,16 @@ __global__ __launch_bounds__(NT) void k_seg_pass_planes(SegPassDev P) {
       }
     }
   }
-  if (P.partials) {
+  if (Q.partials) {
     // fixed-order block reduction: wave sums, then thread 0 adds them in order
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+    double* red = seg_lds_map(smem, Q, (Q.norb + 7) >> 3).red;
     if (lane == 0) red[wave] = acc;
     __syncthreads();
     if (tid == 0) {
       double t = 0.0;
       for (int i = 0; i < nwaves; ++i) t += red[i];
-      P.partials[blk] = t;
+      Q.partials[SEGS ? r * Q.n_seg + si : r] = t;
     }
   }
 }
