@@ -1052,8 +1052,8 @@ namespace {
 // H psi for a DF Hamiltonian.  The one-body term goes either through the
 // eigenbasis of h (two orbital rotations around a diagonal scale, a gate
 // program like the two-body terms) or directly, as sum_pq h_pq E_pq applied by
-// rows of each spin from a sparse table (the beta spin on the transposed
-// state).  Direct is taken when the tables are short (sparse h or few
+// rows of each spin from a sparse table (the beta spin inside rows held in LDS
+// where one fits, else on the transposed state).  Direct is taken when the tables are short (sparse h or few
 // electrons): at most 48 entries per configuration over both spins.
 struct HamAction {
   std::vector<Compiled> cs;  // gate programs: the two-body terms, after the one-body term when it is one
@@ -1063,6 +1063,13 @@ struct HamAction {
     int32_t* src = nullptr;
     double* coef = nullptr;
   } tab[2];
+  // beta rows that fit in LDS: that spin's table by columns (entry k of column
+  // c at k * cols + c, cnt[c] of them) instead of tab[1]
+  struct ColTab {
+    int32_t* cnt = nullptr;
+    int32_t* src = nullptr;
+    double* coef = nullptr;
+  } cols;
   // two-body terms whose basis is exactly the identity (a diagonal Coulomb
   // Hamiltonian's term) ride along in the direct alpha pass as a diagonal
   dev::OneBodyDiag diag{nullptr, nullptr, nullptr, nullptr, 0};
@@ -1111,16 +1118,42 @@ void prepare_one_body(ffx_plan_s& P, const double* h, HamAction& A) {
   }
   A.direct = direct;
   if (!direct) return;
-  for (int sp = 0; sp < 2; ++sp) {
-    HamAction::Tab& d = A.tab[sp];
-    d.off = (int64_t*)A.alloc(t[sp].off.size() * 8);
-    d.src = (int32_t*)A.alloc(t[sp].src.size() * 4);
-    d.coef = (double*)A.alloc(t[sp].coef.size() * 8);
-    HIPCHK(hipMemcpy(d.off, t[sp].off.data(), t[sp].off.size() * 8, hipMemcpyHostToDevice));
-    if (!t[sp].src.empty()) {
-      HIPCHK(hipMemcpy(d.src, t[sp].src.data(), t[sp].src.size() * 4, hipMemcpyHostToDevice));
-      HIPCHK(hipMemcpy(d.coef, t[sp].coef.data(), t[sp].coef.size() * 8, hipMemcpyHostToDevice));
-    }
+  // every table in one allocation and one copy
+  std::vector<char> blob;
+  std::vector<std::pair<void*, size_t>> at;  // where a device pointer goes and its offset
+  auto put = [&](void* dst, const void* h, size_t bytes) {
+    at.emplace_back(dst, blob.size());
+    blob.resize((blob.size() + bytes + 15) / 16 * 16);
+    if (bytes) std::memcpy(blob.data() + at.back().second, h, bytes);
+  };
+  const bool by_cols = dev::onebody_cols_fits(P.c64, P.dim[0], P.dim[1]);
+  for (int sp = 0; sp < (by_cols ? 1 : 2); ++sp) {
+    put(&A.tab[sp].coef, t[sp].coef.data(), t[sp].coef.size() * 8);
+    put(&A.tab[sp].off, t[sp].off.data(), t[sp].off.size() * 8);
+    put(&A.tab[sp].src, t[sp].src.data(), t[sp].src.size() * 4);
+  }
+  if (by_cols) {
+    const OneBodyTable& b = t[1];
+    const size_t db = (size_t)P.dim[1];
+    std::vector<int32_t> cnt(db);
+    int32_t most = 0;
+    for (size_t c = 0; c < db; ++c) most = std::max(most, cnt[c] = (int32_t)(b.off[c + 1] - b.off[c]));
+    std::vector<int32_t> src((size_t)most * db, 0);
+    std::vector<double> coef((size_t)most * db, 0.0);
+    for (size_t c = 0; c < db; ++c)
+      for (int32_t k = 0; k < cnt[c]; ++k) {
+        src[(size_t)k * db + c] = b.src[b.off[c] + k];
+        coef[(size_t)k * db + c] = b.coef[b.off[c] + k];
+      }
+    put(&A.cols.coef, coef.data(), coef.size() * 8);
+    put(&A.cols.src, src.data(), src.size() * 4);
+    put(&A.cols.cnt, cnt.data(), cnt.size() * 4);
+  }
+  char* d = (char*)A.alloc(blob.size());
+  HIPCHK(hipMemcpy(d, blob.data(), blob.size(), hipMemcpyHostToDevice));
+  for (auto& x : at) {
+    char* q = d + x.second;
+    std::memcpy(x.first, &q, sizeof q);
   }
 }
 
@@ -1148,13 +1181,15 @@ void build_ham_action(ffx_plan_s& P, const DFHost& df, const double* h, DecompPo
     }
     if (any) {
       // weight 1/2 (x_a + x_b)^T J (x_a + x_b) as per-string tables A, B and the cross table V
-      double* dJ = (double*)A.alloc((size_t)N * N * 8);
-      HIPCHK(hipMemcpy(dJ, Jsum.data(), (size_t)N * N * 8, hipMemcpyHostToDevice));
-      double* tA = (double*)A.alloc((size_t)P.dim[0] * 8);
-      double* tB = (double*)A.alloc((size_t)P.dim[1] * 8);
-      double* tV = (double*)A.alloc((size_t)N * P.dim[1] * 8);
-      // (row p of V is linear in the beta occupations, with the coefficients J[p])
       std::vector<dev::DiagJobDev> jobs((size_t)N + 2);
+      const size_t nj = jobs.size() * sizeof(dev::DiagJobDev), nJ = (size_t)N * N * 8;
+      char* buf = (char*)A.alloc(nj + nJ + ((size_t)P.dim[0] + (size_t)(N + 1) * P.dim[1]) * 8);
+      auto* dj = (dev::DiagJobDev*)buf;
+      double* dJ = (double*)(buf + nj);
+      double* tA = dJ + (size_t)N * N;
+      double* tB = tA + P.dim[0];
+      double* tV = tB + P.dim[1];
+      // (row p of V is linear in the beta occupations, with the coefficients J[p])
       for (int k = 0; k < N + 2; ++k) {
         dev::DiagJobDev& j = jobs[k];
         j = dev::DiagJobDev{};
@@ -1169,8 +1204,10 @@ void build_ham_action(ffx_plan_s& P, const DFHost& df, const double* h, DecompPo
           j.val = tV + (size_t)(k - 2) * P.dim[1];
         }
       }
-      auto* dj = (dev::DiagJobDev*)A.alloc(jobs.size() * sizeof(dev::DiagJobDev));
-      HIPCHK(hipMemcpy(dj, jobs.data(), jobs.size() * sizeof(dev::DiagJobDev), hipMemcpyHostToDevice));
+      std::vector<char> up(nj + nJ);
+      std::memcpy(up.data(), jobs.data(), nj);
+      std::memcpy(up.data() + nj, Jsum.data(), nJ);
+      HIPCHK(hipMemcpy(buf, up.data(), up.size(), hipMemcpyHostToDevice));
       dev::string_tables(dj, N + 2, (int)std::max(P.dim[0], P.dim[1]), N, s);
       check_launch();
       A.diag = dev::OneBodyDiag{tA, tB, tV, P.d_masks[0], N};
@@ -1183,20 +1220,29 @@ void build_ham_action(ffx_plan_s& P, const DFHost& df, const double* h, DecompPo
   up.commit();
 }
 
-// out = sum_pq h_pq E_pq in from the direct tables; tmp is a state-sized work buffer; in, out, tmp distinct
+// out = sum_pq h_pq E_pq in from the direct tables; tmp is a state-sized work buffer; in, out, tmp distinct.
+// With ch, the result is y of that Chebyshev step with t_cur = in (out is then a work buffer).
 void apply_one_body_direct(ffx_plan_s& P, const HamAction& A, const void* in, void* out, void* tmp,
-                           hipStream_t s) {
+                           const dev::ChebStep* ch, hipStream_t s) {
   const int64_t da = P.dim[0], db = P.dim[1];
-  // beta: on the transposed state, rows = beta configurations
-  dev::transpose(P.c64, in, tmp, da, db, s);
-  check_launch();
-  const dev::OneBodyDiag none{nullptr, nullptr, nullptr, nullptr, 0};
-  dev::onebody_rows(P.c64, tmp, out, nullptr, db, da, A.tab[1].off, A.tab[1].src, A.tab[1].coef, none, s);
-  check_launch();
-  dev::transpose(P.c64, out, tmp, db, da, s);
-  check_launch();
+  const void* beta = out;
+  if (A.cols.cnt) {
+    // beta inside the rows
+    dev::onebody_cols(P.c64, in, out, da, db, A.cols.cnt, A.cols.src, A.cols.coef, s);
+    check_launch();
+  } else {
+    // beta: on the transposed state, rows = beta configurations
+    dev::transpose(P.c64, in, tmp, da, db, s);
+    check_launch();
+    const dev::OneBodyDiag none{nullptr, nullptr, nullptr, nullptr, 0};
+    dev::onebody_rows(P.c64, tmp, out, nullptr, db, da, A.tab[1].off, A.tab[1].src, A.tab[1].coef, none, nullptr, s);
+    check_launch();
+    dev::transpose(P.c64, out, tmp, db, da, s);
+    check_launch();
+    beta = tmp;
+  }
   // alpha, plus the beta part
-  dev::onebody_rows(P.c64, in, out, tmp, da, db, A.tab[0].off, A.tab[0].src, A.tab[0].coef, A.diag, s);
+  dev::onebody_rows(P.c64, in, out, beta, da, db, A.tab[0].off, A.tab[0].src, A.tab[0].coef, A.diag, ch, s);
   check_launch();
 }
 
@@ -1204,7 +1250,7 @@ void apply_one_body_direct(ffx_plan_s& P, const HamAction& A, const void* in, vo
 void apply_ham(ffx_plan_s& P, const HamAction& A, const void* in, void* out, void* tmp, hipStream_t s) {
   size_t k = 0;
   if (A.direct) {
-    apply_one_body_direct(P, A, in, out, tmp, s);
+    apply_one_body_direct(P, A, in, out, tmp, nullptr, s);
   } else {
     execute_program(P, A.cs[k++], in, out, nullptr, s);
   }
@@ -1286,16 +1332,19 @@ int ffx_df_evolve_exact(ffx_plan plan, void* vec, const ffx_df_ham* ham, double 
     check_launch();
     for (int k = 1; k <= K; ++k) {
       // k = 1: T_1 = (H - c) T_0 / r into tcur; k >= 2: T_k = 2 (H - c) T_{k-1} / r - T_{k-2}
-      const void* src = k == 1 ? tprev : tcur;
-      apply_ham(P, A, src, y, tmp, s);
       const cd ck = coef(k);
-      if (k == 1) {
-        dev::cheb_step(P.c64, y, tprev, tcur, vec, n, 1.0 / r, -c / r, 0.0, ck.real(), ck.imag(), s);
+      const void* src = k == 1 ? tprev : tcur;
+      const dev::ChebStep ch{k == 1 ? tcur : tprev, vec, (k == 1 ? 1.0 : 2.0) / r, (k == 1 ? -c : -2.0 * c) / r,
+                             k == 1 ? 0.0 : -1.0, ck.real(), ck.imag()};
+      if (A.direct && A.cs.empty()) {
+        // H is the direct pass alone: its last kernel takes the step
+        apply_one_body_direct(P, A, src, y, tmp, &ch, s);
       } else {
-        dev::cheb_step(P.c64, y, tcur, tprev, vec, n, 2.0 / r, -2.0 * c / r, -1.0, ck.real(), ck.imag(), s);
-        std::swap(tprev, tcur);
+        apply_ham(P, A, src, y, tmp, s);
+        dev::cheb_step(P.c64, y, src, ch.tprev, ch.acc, n, ch.a, ch.b, ch.m, ch.cr, ch.ci, s);
+        check_launch();
       }
-      check_launch();
+      if (k > 1) std::swap(tprev, tcur);
     }
     if (n_matvec) *n_matvec = K;
   });
@@ -1362,7 +1411,7 @@ int ffx_lucj_energy_grad(ffx_plan plan, const ffx_lucj* op, const ffx_df_ham* ha
     // costate lambda = H psi (the one-body term directly from its tables when they are short)
     for (int t = 0; t <= Lt; ++t) {
       if (t == 0 && onebody.direct)
-        apply_one_body_direct(P, onebody, psi, lam, tmp, s);
+        apply_one_body_direct(P, onebody, psi, lam, tmp, nullptr, s);
       else if (t == 0)
         execute_program(P, c_terms[t], psi, lam, nullptr, s);
       else
@@ -1522,7 +1571,7 @@ int ffx_df_chain_energy_grad(ffx_plan plan, const void* vec0, const ffx_df_ham* 
     if (psi_out) HIPCHK(hipMemcpyAsync(psi_out, psi, S, hipMemcpyDeviceToDevice, s));
     for (int t = 0; t <= ob.L; ++t) {
       if (t == 0 && onebody.direct)
-        apply_one_body_direct(P, onebody, psi, lam, tmp, s);
+        apply_one_body_direct(P, onebody, psi, lam, tmp, nullptr, s);
       else if (t == 0)
         execute_program(P, c_terms[t], psi, lam, nullptr, s);
       else

@@ -144,11 +144,23 @@ struct OneBodyDiag {
   const uint32_t* rmasks;
   int norb;
 };
+// a Chebyshev step on y (see cheb_step): t_prev <- a y + b t_cur + m t_prev; acc += (cr + i ci) t_prev
+struct ChebStep {
+  void* tprev;
+  void* acc;
+  double a, b, m, cr, ci;
+};
 // dst[j, :] = sum_{e in [off[j], off[j+1])} coef[e] * src[srow[e], :] (+ w(j, :) src[j, :] when dg.A)
-// (+ add[j, :]); dst must not alias src (add may alias dst)
+// (+ add[j, :]); dst must not alias src (add may alias dst).  With ch, the result is y of that Chebyshev step
+// with t_cur = src instead (dst is not written).
 void onebody_rows(bool c64, const void* src, void* dst, const void* add, int64_t rows, int64_t cols,
                   const int64_t* off, const int32_t* srow, const double* coef, const OneBodyDiag& dg,
-                  hipStream_t stream);
+                  const ChebStep* ch, hipStream_t stream);
+// dst[r, c] = sum_{k < cnt[c]} coef[k * cols + c] * src[r, scol[k * cols + c]]; dst must not alias src.  For rows
+// that fit in LDS (onebody_cols_fits).
+bool onebody_cols_fits(bool c64, int64_t rows, int64_t cols);
+void onebody_cols(bool c64, const void* src, void* dst, int64_t rows, int64_t cols, const int32_t* cnt,
+                  const int32_t* scol, const double* coef, hipStream_t stream);
 // y += x
 void axpy(bool c64, const void* x, void* y, int64_t n, hipStream_t stream);
 // vec[i_a, i_b] = a[i_a] * b[i_b] (a, b complex double)

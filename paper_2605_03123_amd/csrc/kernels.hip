@@ -590,85 +590,218 @@ void dist2(bool c64, const void* x, const void* y, int64_t n, double* partials, 
   hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, s, partials, nb, 1, out);
 }
 
-// One-body operator of the row spin applied by rows:
-//   dst[j, :] = sum_{e in [off[j], off[j+1])} coef[e] * src[srow[e], :]  (+ add[j, :])
-// One block per (row j, tile of 2048 columns); the entries of row j are the
-// same for the whole block.  FP64 accumulation, one rounding to the state type.
-constexpr int kOneBodyPer = 8;
-// With dg.A set, the diagonal term w(j, col) src[j, col] is added too, w = A[j] + B[col] +
-// sum_{p in row string j} V[p][col] (the tables of a diagonal weight, k_diag_tables).
-template <class R>
+// One-body operator of the row spin:
+//   dst[j, :] = sum_{e in [off[j], off[j+1])} coef[e] * src[srow[e], :]
+//               (+ w(j, :) src[j, :] with dg.A) (+ add[j, :])
+// with w(j, col) = A[j] + B[col] + sum_{p in row string j} V[p][col].  FP64
+// accumulation, one rounding to the state's type.  With CHEB the result y is
+// not stored but taken into a Chebyshev step (k_cheb_step's, with t_cur = src).
+//
+// A wave takes one row and 64 columns (a kilobyte of each source row in
+// complex128); its entries are the same in every lane.  Every row is read by
+// as many others as it has entries (13 to 17 on the lattices), so the order of
+// the blocks decides what memory sees: all rows of one 64-column tile before
+// the next, so that a tile stays in a cache.  Where a tile fits the 4 MB L2 of
+// an XCD (block b runs on XCD b mod 8) each XCD has tiles of its own;
+// otherwise all XCDs work through one tile, which the 256 MB cache holds.
+// Bound by memory: at 2024 x 2024 complex128 with the Chebyshev step 73 us for
+// 393 MB that have to move, 5.3 TB/s (blocks of one row and 2048 columns, rows
+// in order, re-read their sources from beyond L2: 126 us, and 56 us for the
+// step in a kernel of its own).
+constexpr int kOneBodyU = 8;
+template <class R, bool CHEB>
 __global__ __launch_bounds__(256) void k_onebody_rows(const typename V2T<R>::type* __restrict__ src,
                                                       typename V2T<R>::type* dst,
                                                       const typename V2T<R>::type* add, int64_t rows,
-                                                      int64_t cols, int64_t tiles, const int64_t* __restrict__ off,
+                                                      int64_t cols, unsigned row_blocks, unsigned tiles, int per_xcd,
+                                                      const int64_t* __restrict__ off,
                                                       const int32_t* __restrict__ srow,
-                                                      const double* __restrict__ coef, OneBodyDiag dg) {
-  const int64_t j = (int64_t)blockIdx.x / tiles;
-  const int64_t c0 = ((int64_t)blockIdx.x % tiles) * (256 * kOneBodyPer) + threadIdx.x;
-  if (j >= rows) return;
-  double ar[kOneBodyPer], ai[kOneBodyPer];
+                                                      const double* __restrict__ coef, OneBodyDiag dg,
+                                                      ChebStep ch) {
+  using V = typename V2T<R>::type;
+  const unsigned b = per_xcd ? blockIdx.x >> 3 : blockIdx.x;
+  const unsigned tile = per_xcd ? (blockIdx.x & 7) + 8 * (b / row_blocks) : b / row_blocks;
+  const int64_t j = (int64_t)(b % row_blocks) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (tile >= tiles || j >= rows) return;
+  const int64_t col = (int64_t)tile * 64 + (threadIdx.x & 63);
+  const bool in = col < cols;
+  const V* base = src + (in ? col : cols - 1);
+  double ar = 0.0, ai = 0.0;
+  const int64_t e1 = uniform_load(off + j + 1);
+  for (int64_t e = uniform_load(off + j); e < e1; e += kOneBodyU) {
+    V v[kOneBodyU];
 #pragma unroll
-  for (int k = 0; k < kOneBodyPer; ++k) ar[k] = ai[k] = 0.0;
-  const int64_t e1 = off[j + 1];
-  for (int64_t e = off[j]; e < e1; ++e) {
-    const typename V2T<R>::type* sp = src + (int64_t)srow[e] * cols;
-    const double c = coef[e];
+    for (int u = 0; u < kOneBodyU; ++u)
+      if (e + u < e1) v[u] = base[(int64_t)uniform_load(srow + e + u) * cols];
 #pragma unroll
-    for (int k = 0; k < kOneBodyPer; ++k) {
-      const int64_t col = c0 + 256 * k;
-      if (col < cols) {
-        const auto v = sp[col];
-        ar[k] += c * (double)v.x;
-        ai[k] += c * (double)v.y;
+    for (int u = 0; u < kOneBodyU; ++u)
+      if (e + u < e1) {
+        const double c = uniform_load(coef + e + u);
+        ar += c * (double)v[u].x;
+        ai += c * (double)v[u].y;
       }
-    }
   }
+  if (!in) return;
+  V self{};
+  if (dg.A || CHEB) self = src[j * cols + col];
   if (dg.A) {
-    const double wa = dg.A[j];
     const uint32_t m = dg.rmasks[j];
-#pragma unroll
-    for (int k = 0; k < kOneBodyPer; ++k) {
-      const int64_t col = c0 + 256 * k;
-      if (col < cols) {
-        double w = wa + dg.B[col];
-        for (int p = 0; p < dg.norb; ++p)
-          if ((m >> p) & 1) w += dg.V[(int64_t)p * cols + col];
-        const auto v = src[j * cols + col];
-        ar[k] += w * (double)v.x;
-        ai[k] += w * (double)v.y;
-      }
-    }
+    double w = dg.A[j] + dg.B[col];
+    for (int p = 0; p < dg.norb; ++p)
+      if ((m >> p) & 1) w += dg.V[(int64_t)p * cols + col];
+    ar += w * (double)self.x;
+    ai += w * (double)self.y;
   }
-#pragma unroll
-  for (int k = 0; k < kOneBodyPer; ++k) {
-    const int64_t col = c0 + 256 * k;
-    if (col < cols) {
-      double xr = ar[k], xi = ai[k];
-      if (add) {
-        const auto a = add[j * cols + col];
-        xr += (double)a.x;
-        xi += (double)a.y;
-      }
-      typename V2T<R>::type o;
-      o.x = (R)xr;
-      o.y = (R)xi;
-      dst[j * cols + col] = o;
+  if (add) {
+    const V a = add[j * cols + col];
+    ar += (double)a.x;
+    ai += (double)a.y;
+  }
+  V o;
+  o.x = (R)ar;
+  o.y = (R)ai;
+  if constexpr (CHEB) {
+    V* tprev = (V*)ch.tprev + j * cols + col;
+    V* acc = (V*)ch.acc + j * cols + col;
+    double xr = ch.a * (double)o.x + ch.b * (double)self.x;
+    double xi = ch.a * (double)o.y + ch.b * (double)self.y;
+    if (ch.m != 0.0) {  // m = 0: t_prev holds no value yet (first step)
+      const V vp = *tprev;
+      xr += ch.m * (double)vp.x;
+      xi += ch.m * (double)vp.y;
     }
+    const V va = *acc;
+    V tn, an;
+    tn.x = (R)xr;
+    tn.y = (R)xi;
+    an.x = (R)((double)va.x + (ch.cr * xr - ch.ci * xi));
+    an.y = (R)((double)va.y + (ch.cr * xi + ch.ci * xr));
+    *tprev = tn;
+    *acc = an;
+  } else {
+    dst[j * cols + col] = o;
   }
 }
 
-void onebody_rows(bool c64, const void* src, void* dst, const void* add, int64_t rows, int64_t cols,
-                  const int64_t* off, const int32_t* srow, const double* coef, const OneBodyDiag& dg, hipStream_t s) {
-  if (rows <= 0 || cols <= 0) return;
-  const int64_t tiles = (cols + 256 * kOneBodyPer - 1) / (256 * kOneBodyPer);
-  const dim3 g((unsigned)(rows * tiles));
-  if (c64)
-    hipLaunchKernelGGL(k_onebody_rows<float>, g, dim3(256), 0, s, (const zc64*)src, (zc64*)dst, (const zc64*)add,
-                       rows, cols, tiles, off, srow, coef, dg);
+template <class R>
+static void onebody_rows_r(const void* src, void* dst, const void* add, int64_t rows, int64_t cols,
+                           const int64_t* off, const int32_t* srow, const double* coef, const OneBodyDiag& dg,
+                           const ChebStep* ch, hipStream_t s) {
+  using V = typename V2T<R>::type;
+  const unsigned row_blocks = (unsigned)((rows + 3) / 4), tiles = (unsigned)((cols + 63) / 64);
+  // a tile and what streams past it share an XCD's L2; fewer tiles than XCDs would leave some idle
+  const bool per_xcd = tiles >= 8 && rows * 64 * (int64_t)sizeof(V) <= (3 << 20);
+  const unsigned blocks = per_xcd ? (tiles + 7) / 8 * 8 * row_blocks : tiles * row_blocks;
+  if (ch)
+    hipLaunchKernelGGL((k_onebody_rows<R, true>), dim3(blocks), dim3(256), 0, s, (const V*)src, (V*)nullptr,
+                       (const V*)add, rows, cols, row_blocks, tiles, (int)per_xcd, off, srow, coef, dg, *ch);
   else
-    hipLaunchKernelGGL(k_onebody_rows<double>, g, dim3(256), 0, s, (const zc128*)src, (zc128*)dst,
-                       (const zc128*)add, rows, cols, tiles, off, srow, coef, dg);
+    hipLaunchKernelGGL((k_onebody_rows<R, false>), dim3(blocks), dim3(256), 0, s, (const V*)src, (V*)dst,
+                       (const V*)add, rows, cols, row_blocks, tiles, (int)per_xcd, off, srow, coef, dg, ChebStep{});
+}
+
+void onebody_rows(bool c64, const void* src, void* dst, const void* add, int64_t rows, int64_t cols,
+                  const int64_t* off, const int32_t* srow, const double* coef, const OneBodyDiag& dg,
+                  const ChebStep* ch, hipStream_t s) {
+  if (rows <= 0 || cols <= 0) return;
+  if (c64)
+    onebody_rows_r<float>(src, dst, add, rows, cols, off, srow, coef, dg, ch, s);
+  else
+    onebody_rows_r<double>(src, dst, add, rows, cols, off, srow, coef, dg, ch, s);
+}
+
+// One-body operator of the column spin: dst[r, c] = sum_{k < cnt[c]}
+// coef[k * cols + c] * src[r, scol[k * cols + c]].  A block holds RB whole rows
+// in LDS and gathers from them, so the state is read and written once and
+// needs no transposes around it; the entry table (entry k of all columns side
+// by side, so that lanes read it coalesced) is read once for RB rows.  The sums
+// run in the entries' order, as in k_onebody_rows.
+template <class R, int RB>
+__global__ __launch_bounds__(512) void k_onebody_cols(const typename V2T<R>::type* __restrict__ src,
+                                                      typename V2T<R>::type* __restrict__ dst, int64_t rows, int cols,
+                                                      const int32_t* __restrict__ cnt,
+                                                      const int32_t* __restrict__ scol,
+                                                      const double* __restrict__ coef) {
+  using V = typename V2T<R>::type;
+  extern __shared__ __align__(16) char smem[];
+  V* row = (V*)smem;
+  const int64_t r0 = (int64_t)blockIdx.x * RB;
+  const int nr = (int)min((int64_t)RB, rows - r0);
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  stage_in<8>(row, src + r0 * cols, nr * cols, tid, nthr);
+  __syncthreads();
+  for (int c = tid; c < cols; c += nthr) {
+    double ar[RB], ai[RB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) ar[r] = ai[r] = 0.0;
+    const int n = cnt[c];
+    const int32_t* sc = scol + c;
+    const double* co = coef + c;
+#pragma unroll 4
+    for (int k = 0; k < n; ++k) {
+      const int s = sc[(int64_t)k * cols];
+      const double f = co[(int64_t)k * cols];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const V v = row[min(r, nr - 1) * cols + s];
+        ar[r] += f * (double)v.x;
+        ai[r] += f * (double)v.y;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+      if (r < nr) {
+        V o;
+        o.x = (R)ar[r];
+        o.y = (R)ai[r];
+        dst[(r0 + r) * cols + c] = o;
+      }
+  }
+}
+
+template <class R, int RB>
+static void launch_onebody_cols(const void* src, void* dst, int64_t rows, int cols, const int32_t* cnt,
+                                const int32_t* scol, const double* coef, hipStream_t s) {
+  using V = typename V2T<R>::type;
+  auto k = k_onebody_cols<R, RB>;
+  (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  const int threads = std::min(512, (cols + 63) / 64 * 64);
+  hipLaunchKernelGGL(k, dim3((unsigned)((rows + RB - 1) / RB)), dim3(threads), (size_t)RB * cols * sizeof(V), s,
+                     (const V*)src, (V*)dst, rows, cols, cnt, scol, coef);
+}
+
+// Rows per block: as many as fit 64 KB (two blocks to a compute unit) while
+// the launch still has two blocks for each of 256 units; 0: a row exceeds LDS.
+static int onebody_cols_rows(size_t elem, int64_t rows, int64_t cols) {
+  if ((size_t)cols * elem > 150 * 1024) return 0;
+  int rb = 1;
+  while (rb < 8 && 2 * rb * cols * elem <= 64 * 1024 && rows >= 1024 * rb) rb *= 2;
+  return rb;
+}
+
+bool onebody_cols_fits(bool c64, int64_t rows, int64_t cols) {
+  return onebody_cols_rows(c64 ? 8 : 16, rows, cols) > 0;
+}
+
+template <class R>
+static void onebody_cols_r(int rb, const void* src, void* dst, int64_t rows, int cols, const int32_t* cnt,
+                           const int32_t* scol, const double* coef, hipStream_t s) {
+  switch (rb) {
+    case 1: launch_onebody_cols<R, 1>(src, dst, rows, cols, cnt, scol, coef, s); break;
+    case 2: launch_onebody_cols<R, 2>(src, dst, rows, cols, cnt, scol, coef, s); break;
+    case 4: launch_onebody_cols<R, 4>(src, dst, rows, cols, cnt, scol, coef, s); break;
+    default: launch_onebody_cols<R, 8>(src, dst, rows, cols, cnt, scol, coef, s); break;
+  }
+}
+
+void onebody_cols(bool c64, const void* src, void* dst, int64_t rows, int64_t cols, const int32_t* cnt,
+                  const int32_t* scol, const double* coef, hipStream_t s) {
+  if (rows <= 0 || cols <= 0) return;
+  const int rb = onebody_cols_rows(c64 ? 8 : 16, rows, cols);
+  if (c64)
+    onebody_cols_r<float>(rb, src, dst, rows, (int)cols, cnt, scol, coef, s);
+  else
+    onebody_cols_r<double>(rb, src, dst, rows, (int)cols, cnt, scol, coef, s);
 }
 
 template <class R>

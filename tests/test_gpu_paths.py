@@ -3,6 +3,7 @@
 Amplitudes: 1e-12 (complex128) and 1e-5 (complex64) absolute on normalised states, the bounds of every gate."""
 import numpy as np
 import pytest
+import scipy.sparse as sp
 import torch
 
 from oracle import gates as og
@@ -63,3 +64,35 @@ def test_rotations_around_a_phase(ffx, norb, nelec, dtype, real):
     ref = og.apply_diag_coulomb_evolution(ref, J, 0.9, norb, nelec)
     ref = og.apply_orbital_rotation(ref, U, norb, nelec)
     assert np.max(np.abs(_ref(out) - ref)) <= TOL[dtype]
+
+
+def _hopping(h, norb, n):
+    """sum_pq h_pq a+_p a_q on one spin as a sparse matrix."""
+    strs, addr = ost.strings(norb, n), ost.address_map(norb, n)
+    rows, cols, vals = [], [], []
+    for q, p in zip(*np.nonzero(h)):
+        for c, m in enumerate(int(x) for x in strs):
+            if (m >> q) & 1 and (p == q or not (m >> p) & 1):
+                rows.append(addr[m ^ (1 << q) ^ (1 << p) if p != q else m])
+                cols.append(c)
+                vals.append(h[p, q] * ost.excitation_sign(m, int(p), int(q)))
+    return sp.csr_matrix((vals, (rows, cols)), shape=(len(strs), len(strs)))
+
+
+# the one-body operator from its tables: 1, 2, 4 and 8 rows of a state per block with a ragged last block, a last
+# column tile of a few columns, column tiles per XCD and shared, rows that fit LDS in both types, in complex64 only
+# and in neither
+@pytest.mark.parametrize("norb,nelec", [(9, (4, 2)), (13, (5, 5)), (13, (5, 3)), (14, (6, 3)), (14, (7, 4)),
+                                        (15, (7, 1)), (24, (1, 4)), (20, (1, 6)), (6, (3, 0))])
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+def test_one_body_tables(ffx, monkeypatch, norb, nelec, dtype):
+    monkeypatch.setenv("FFX_ONEBODY", "direct")
+    r = synth.rng([47, norb, nelec[0], nelec[1]])
+    v = _state(r, norb, nelec, dtype)
+    ham = synth.hubbard_2d(norb, 1)
+    out = ffx.apply_df_hamiltonian(v, ham, norb, nelec)
+    x = _ref(v)
+    na, nb = (ost.occupations(norb, n).astype(np.float64) for n in nelec)
+    two = 0.5 * ham.J[0, 0, 0] * (nelec[0] + nelec[1] + 2.0 * (na @ nb.T))
+    ref = _hopping(ham.h, norb, nelec[0]) @ x + (_hopping(ham.h, norb, nelec[1]) @ x.T).T + two * x
+    assert np.max(np.abs(_ref(out) - ref)) <= TOL[dtype] * max(1.0, float(np.abs(ref).max()))
