@@ -278,6 +278,7 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
     if (const char* e = std::getenv("FFX_DENSE")) P->dense_max_dim = std::atoll(e) > 0 ? std::atoll(e) : 0;
     if (std::getenv("FFX_SEG_MAX")) P->dense_max_dim = 0;
     if (P->c64 || P->n[0] > 8 || P->n[1] > 8) P->dense_max_dim = 0;
+    if (P->takes_dense()) P->dense_ws = P->dalloc((size_t)ffx_workspace_bytes(P.get(), 3));
     if (const char* e = std::getenv("FFX_SEG_MAX")) {  // smaller segments, for tests
       int64_t v = std::atoll(e);
       if (v >= 1 && v < max_elems) max_elems = v;
@@ -664,10 +665,9 @@ int ffx_apply_orbital_rotation(ffx_plan plan, void* vec, const double* U_a, cons
       throw Error(FFX_EINVAL, "non-finite U");
     DeviceGuard dg(plan->device);
     hipStream_t s = as_stream(stream);
-    if (plan->dim[0] <= plan->dense_max_dim && plan->dim[1] <= plan->dense_max_dim) {
+    if (plan->takes_dense()) {
       // small sector: the dense form is the faster one (measured)
       check_rotation_args(N, U_a, U_b);
-      if (!plan->dense_ws) plan->dense_ws = plan->dalloc((size_t)ffx_workspace_bytes(plan, 3));
       rotate_dense(*plan, vec, U_a, U_b, plan->dense_ws, s);
       return;
     }
@@ -699,12 +699,16 @@ void rotate_dense(ffx_plan_s& P, void* vec, const double* U_a, const double* U_b
     void* Ca = ws;
     void* Cb = ws + r256(da * da * 16);
     void* T = (char*)Cb + r256(db * db * 16);
-    Upload up(&P, s);
-    const double* dUa = up.put(U_a, (size_t)2 * N * N);
-    const double* dUb = up.put(Ubp, (size_t)2 * N * N);
-    up.commit();
-    dev::compound_matrix(P.d_masks[0], da, P.n[0], N, dUa, Ca, s);
-    dev::compound_matrix(P.d_masks[1], db, P.n[1], N, dUb, Cb, s);
+    if (!U_b && P.n[0] == P.n[1]) Cb = Ca;
+    const double* hU[2] = {U_a, Ubp};
+    const double* dU[2] = {nullptr, nullptr};
+    if (N > dev::compound_arg_orbitals()) {
+      Upload up(&P, s);
+      for (int k = 0; k < 2; ++k) dU[k] = up.put(hU[k], (size_t)2 * N * N);
+      up.commit();
+    }
+    void* const C[2] = {Ca, Cb};
+    dev::compound_matrices(P.d_masks, P.dim, P.n, N, hU, dU, C, s);
     // T = Gamma C_b^T (element (k, n) of C_b^T is C_b[n][k]), then Gamma' = C_a T
     dev::zgemm_mfma(vec, db, Cb, 1, db, T, db, (int)da, (int)db, (int)db, s);
     dev::zgemm_mfma(Ca, da, T, db, 1, vec, db, (int)da, (int)db, (int)da, s);

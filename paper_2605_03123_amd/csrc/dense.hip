@@ -2,17 +2,19 @@
 // compound matrices C_n(U)[J, I] = det U[J, I] (rows J and columns I the occupied orbitals of two
 // configurations, ascending).  It is the plain definition of script-U(U) on the sector, evaluated as
 // two complex matrix products on the FP64 matrix cores; the Givens sweeps reach the same result with
-// 20 n (N - n) d^2 flops against this form's 16 d^3, so it is built to be measured against them on
-// small sectors (d <= a few thousand), not as the default path.
+// 20 n (N - n) d^2 flops against this form's 16 d^3, so it is taken
+// for small sectors only, where both are bound by latency.
 //   * k_compound<n>: one thread per entry, the n x n minor gathered into registers and reduced by
-//     Gaussian elimination with partial pivoting in complex FP64.
-//   * k_zgemm_mfma: Y = A B (complex128, row-major A and Y, B addressed through two strides so that
-//     C^T needs no copy) in 64 x 64 output tiles per block of four waves, 16-deep slices of A and B
-//     staged in LDS (real and imaginary parts apart), v_mfma_f64_16x16x4 with the real and imaginary
-//     accumulators of each 16 x 16 tile (four products per k step).
+//     Gaussian elimination with partial pivoting in complex FP64; both spins in one launch where their
+//     electron numbers are n or n + 1.
+//   * Y = A B (complex128, row-major A and Y, B addressed through two strides so that C^T needs no
+//     copy) by v_mfma_f64_16x16x4, the real and imaginary accumulators of a 16 x 16 tile taking four
+//     products per k step: k_zgemm_tile for small products, k_zgemm_mfma for large ones.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
+#include <cstring>
 
 #include "dev_common.h"
 #include "device.h"
@@ -20,17 +22,28 @@
 namespace ffx {
 namespace dev {
 
+// U (row-major complex norb x norb) from a buffer or, for up to kArgOrb
+// orbitals, out of the kernel's own arguments: no upload before the launch.
+constexpr int kArgOrb = 11;
+struct CompoundSpin {
+  const uint32_t* masks;
+  const double* U;  // null: the arguments hold it
+  zc128* C;
+  int d, n;
+};
+struct CompoundArgs {
+  CompoundSpin sp[2];
+  int norb;
+  int which[2];  // the matrix in u that spin blockIdx.y takes
+  double u[2][2 * kArgOrb * kArgOrb];
+};
+
 template <int NE>
-__global__ __launch_bounds__(256) void k_compound(const uint32_t* __restrict__ masks, int64_t d, int norb,
-                                                  const double* __restrict__ U, zc128* __restrict__ C) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= d * d) return;
-  const int64_t J = idx / d, I = idx - J * d;
+__device__ __forceinline__ zc128 minor_det(uint32_t mj, uint32_t mi, int norb, const double* U) {
   if constexpr (NE == 0) {
-    C[idx] = zc128{1.0, 0.0};
+    return zc128{1.0, 0.0};
   } else {
     int r[NE], c[NE];
-    uint32_t mj = masks[J], mi = masks[I];
 #pragma unroll
     for (int k = 0; k < NE; ++k) {
       r[k] = __builtin_ctz(mj);
@@ -93,24 +106,62 @@ __global__ __launch_bounds__(256) void k_compound(const uint32_t* __restrict__ m
         }
       }
     }
-    C[idx] = zc128{dr, di};
+    return zc128{dr, di};
   }
 }
 
-void compound_matrix(const uint32_t* masks, int64_t d, int n, int norb, const double* U, void* C, hipStream_t s) {
-  const dim3 g((unsigned)((d * d + 255) / 256)), b(256);
-  zc128* out = (zc128*)C;
-  switch (n) {
-    case 0: hipLaunchKernelGGL(k_compound<0>, g, b, 0, s, masks, d, norb, U, out); break;
-    case 1: hipLaunchKernelGGL(k_compound<1>, g, b, 0, s, masks, d, norb, U, out); break;
-    case 2: hipLaunchKernelGGL(k_compound<2>, g, b, 0, s, masks, d, norb, U, out); break;
-    case 3: hipLaunchKernelGGL(k_compound<3>, g, b, 0, s, masks, d, norb, U, out); break;
-    case 4: hipLaunchKernelGGL(k_compound<4>, g, b, 0, s, masks, d, norb, U, out); break;
-    case 5: hipLaunchKernelGGL(k_compound<5>, g, b, 0, s, masks, d, norb, U, out); break;
-    case 6: hipLaunchKernelGGL(k_compound<6>, g, b, 0, s, masks, d, norb, U, out); break;
-    case 7: hipLaunchKernelGGL(k_compound<7>, g, b, 0, s, masks, d, norb, U, out); break;
-    case 8: hipLaunchKernelGGL(k_compound<8>, g, b, 0, s, masks, d, norb, U, out); break;
-    default: break;
+template <int LO>
+__global__ __launch_bounds__(256) void k_compound(CompoundArgs) {
+  extern __shared__ double su[];
+  // (through the argument segment's address: indexed by lane, the struct itself would be copied to scratch)
+  const CompoundArgs* P = (const CompoundArgs*)(uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  const CompoundSpin sp = uniform_load(P->sp + blockIdx.y);
+  const int norb = P->norb;
+  const double* U = sp.U ? sp.U : P->u[P->which[blockIdx.y]];
+  for (int i = threadIdx.x; i < 2 * norb * norb; i += 256) su[i] = U[i];
+  __syncthreads();
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x, d = sp.d;
+  if (idx >= d * d) return;
+  const int64_t J = idx / d, I = idx - J * d;
+  const uint32_t mj = sp.masks[J], mi = sp.masks[I];
+  sp.C[idx] = sp.n == LO ? minor_det<LO>(mj, mi, norb, su) : minor_det<LO + 1>(mj, mi, norb, su);
+}
+
+int compound_arg_orbitals() { return kArgOrb; }
+
+void compound_matrices(const uint32_t* const masks[2], const int64_t d[2], const int n[2], int norb,
+                       const double* const hU[2], const double* const dU[2], void* const C[2], hipStream_t s) {
+  CompoundArgs a;
+  a.norb = norb;
+  for (int k = 0; k < 2; ++k) {
+    a.sp[k] = CompoundSpin{masks[k], dU[k], (zc128*)C[k], (int)d[k], n[k]};
+    a.which[k] = k;
+    if (!dU[k]) std::memcpy(a.u[k], hU[k], sizeof(double) * 2 * norb * norb);
+  }
+  auto launch = [&](const CompoundArgs& q, int lo, int64_t dm, int spins) {
+    const dim3 g((unsigned)((dm * dm + 255) / 256), (unsigned)spins), b(256);
+    const size_t lds = sizeof(double) * 2 * norb * norb;
+    switch (lo) {
+      case 0: hipLaunchKernelGGL(k_compound<0>, g, b, lds, s, q); break;
+      case 1: hipLaunchKernelGGL(k_compound<1>, g, b, lds, s, q); break;
+      case 2: hipLaunchKernelGGL(k_compound<2>, g, b, lds, s, q); break;
+      case 3: hipLaunchKernelGGL(k_compound<3>, g, b, lds, s, q); break;
+      case 4: hipLaunchKernelGGL(k_compound<4>, g, b, lds, s, q); break;
+      case 5: hipLaunchKernelGGL(k_compound<5>, g, b, lds, s, q); break;
+      case 6: hipLaunchKernelGGL(k_compound<6>, g, b, lds, s, q); break;
+      default: hipLaunchKernelGGL(k_compound<7>, g, b, lds, s, q); break;
+    }
+  };
+  const int lo = std::min(std::min(n[0], n[1]), 7);
+  if (C[0] == C[1]) {
+    launch(a, lo, d[0], 1);
+  } else if (std::max(n[0], n[1]) <= lo + 1) {
+    launch(a, lo, std::max(d[0], d[1]), 2);
+  } else {
+    launch(a, std::min(n[0], 7), d[0], 1);
+    a.sp[0] = a.sp[1];
+    a.which[0] = 1;
+    launch(a, std::min(n[1], 7), d[1], 1);
   }
 }
 
@@ -121,6 +172,55 @@ void compound_matrix(const uint32_t* masks, int64_t d, int n, int norb, const do
 // into two accumulators per 16 x 16 tile.
 // ---------------------------------------------------------------------------
 typedef double zg_d4 __attribute__((ext_vector_type(4)));
+
+// One 16 x 16 output tile per block, the k steps dealt to its four waves and
+// their sums added in wave order.  Operands come straight from memory: a step's
+// 2 KB cost 256 cycles of matrix work, which the L2 keeps up with.  For
+// products with few tiles of 64 x 64, which leave most compute units idle.  70^3:
+// 4.4 us (k_zgemm_mfma: 15.3 us in 4 blocks); 330^3 12 us (59 us).
+constexpr int kZU = 4;  // k steps whose operands are requested together
+__global__ __launch_bounds__(256) void k_zgemm_tile(const zc128* __restrict__ A, int64_t lda,
+                                                    const zc128* __restrict__ B, int64_t sbk, int64_t sbn,
+                                                    zc128* __restrict__ Y, int64_t ldy, int M, int N, int K) {
+  __shared__ zc128 part[4][256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
+  const int r = lane & 15, q = lane >> 4;
+  // rows and columns past the edge repeat the last one and are not stored
+  const zc128* a = A + (int64_t)min(m0 + r, M - 1) * lda;
+  const zc128* b = B + (int64_t)min(n0 + r, N - 1) * sbn;
+  zg_d4 re{0.0, 0.0, 0.0, 0.0}, im = re;
+  for (int k0 = 4 * wave; k0 < K; k0 += 16 * kZU) {
+    zc128 av[kZU], bv[kZU];
+#pragma unroll
+    for (int u = 0; u < kZU; ++u) {
+      const int k = k0 + 16 * u + q, kc = min(k, K - 1);
+      av[u] = a[kc];
+      bv[u] = b[(int64_t)kc * sbk];
+      if (k >= K) av[u] = bv[u] = zc128{0.0, 0.0};
+    }
+#pragma unroll
+    for (int u = 0; u < kZU; ++u) {
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u].x, bv[u].x, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u].x, bv[u].y, im, 0, 0, 0);
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[u].y, bv[u].y, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u].y, bv[u].x, im, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) part[wave][16 * (q + 4 * t) + r] = zc128{re[t], im[t]};
+  __syncthreads();
+  const int gm = m0 + (tid >> 4), gn = n0 + (tid & 15);
+  if (gm >= M || gn >= N) return;
+  zc128 y = part[0][tid];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) {
+    y.x += part[w][tid].x;
+    y.y += part[w][tid].y;
+  }
+  Y[(int64_t)gm * ldy + gn] = y;
+}
+
 constexpr int kGT = 64;  // output tile edge
 constexpr int kGK = 16;  // k slice
 
@@ -192,9 +292,19 @@ __global__ __launch_bounds__(256) void k_zgemm_mfma(const zc128* __restrict__ A,
       }
 }
 
+// 64 x 64 tiles once they fill the compute units (924^3, 225 tiles: 158 us in
+// them, 152 us in 16 x 16 tiles; above, the smaller tiles read operands too often)
+constexpr unsigned kTileBlocks = 256;
+
 void zgemm_mfma(const void* A, int64_t lda, const void* B, int64_t sbk, int64_t sbn, void* Y, int64_t ldy, int M,
                 int N, int K, hipStream_t s) {
   const dim3 g((unsigned)((N + kGT - 1) / kGT), (unsigned)((M + kGT - 1) / kGT)), b(256);
+  if (g.x * g.y < kTileBlocks) {
+    const dim3 gt((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16));
+    hipLaunchKernelGGL(k_zgemm_tile, gt, b, 0, s, (const zc128*)A, lda, (const zc128*)B, sbk, sbn, (zc128*)Y, ldy, M,
+                       N, K);
+    return;
+  }
   hipLaunchKernelGGL(k_zgemm_mfma, g, b, 0, s, (const zc128*)A, lda, (const zc128*)B, sbk, sbn, (zc128*)Y, ldy, M, N,
                      K);
 }

@@ -123,7 +123,12 @@ int sample_state(bool c64, const void* vec, int64_t n, double* bs, double* pre, 
 // configurations (masks, d of them; U complex norb x norb, device), and the
 // complex128 product Y = A B on the FP64 matrix cores (A row-major with leading
 // dimension lda; element (k, n) of B at B[k * sbk + n * sbn]; Y row-major, ldy).
-void compound_matrix(const uint32_t* masks, int64_t d, int n, int norb, const double* U, void* C, hipStream_t s);
+// Both spins' compound matrices; U comes from the device (dU[k]) or, null there
+// and norb <= compound_arg_orbitals(), from the host (hU[k], read by the call).
+// C[0] == C[1]: one matrix for both, spin 0's.
+int compound_arg_orbitals();
+void compound_matrices(const uint32_t* const masks[2], const int64_t d[2], const int n[2], int norb,
+                       const double* const hU[2], const double* const dU[2], void* const C[2], hipStream_t s);
 void zgemm_mfma(const void* A, int64_t lda, const void* B, int64_t sbk, int64_t sbn, void* Y, int64_t ldy, int M,
                 int N, int K, hipStream_t s);
 // The allocation-free sampler's block sums and prefix live in a static device

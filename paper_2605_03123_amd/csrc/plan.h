@@ -133,10 +133,12 @@ struct ffx_plan_s {
   int* rank_hi = nullptr;
   bool rdm_pairs = false;  // transition one-body matrices from row pairs at any size
   // standalone orbital rotations of complex128 sectors with at most this many
-  // configurations per spin take the dense form on the matrix cores (measured
-  // faster than the Givens sweeps at 70 configurations, even at 252, slower above)
-  int64_t dense_max_dim = 128;
-  void* dense_ws = nullptr;  // its compound matrices and intermediate, allocated on first use
+  // configurations per spin take the dense form on the matrix cores.  Device
+  // time of one rotation, dense against Givens sweeps: 12 and 57 us at 252
+  // configurations, 32 and 56 at 330, 64 and 57 at 462, 350 and 91 at 924.
+  int64_t dense_max_dim = 384;
+  void* dense_ws = nullptr;  // its compound matrices and intermediate
+  bool takes_dense() const { return dim[0] <= dense_max_dim && dim[1] <= dense_max_dim; }
   // per column spin: the (n-1)-electron strings for the matrix-core transition
   // one-body kernel, grouped by their top occupation, built on first use
   struct RdmStrings {

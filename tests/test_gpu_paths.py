@@ -96,3 +96,20 @@ def test_one_body_tables(ffx, monkeypatch, norb, nelec, dtype):
     two = 0.5 * ham.J[0, 0, 0] * (nelec[0] + nelec[1] + 2.0 * (na @ nb.T))
     ref = _hopping(ham.h, norb, nelec[0]) @ x + (_hopping(ham.h, norb, nelec[1]) @ x.T).T + two * x
     assert np.max(np.abs(_ref(out) - ref)) <= TOL[dtype] * max(1.0, float(np.abs(ref).max()))
+
+
+# rotations in the dense form: sectors below one 16 x 16 tile, with remainders of tile and k step, the largest that
+# take it; electron numbers that share the compound launch, that do not, and 8 of them; more orbitals than the kernel
+# arguments hold; empty spins
+@pytest.mark.parametrize("norb,nelec", [(2, (1, 1)), (4, (2, 2)), (5, (2, 3)), (8, (4, 4)), (8, (1, 4)), (9, (8, 8)),
+                                        (9, (8, 2)), (10, (5, 5)), (11, (4, 3)), (12, (3, 2)), (14, (2, 0)),
+                                        (20, (1, 2))])
+@pytest.mark.parametrize("both", [True, False])
+def test_dense_rotation_of_small_sectors(ffx, norb, nelec, both):
+    r = synth.rng([53, norb, nelec[0], nelec[1], int(both)])
+    v = _state(r, norb, nelec, torch.complex128)
+    U = synth.random_unitary(r, norb)
+    U_b = synth.random_unitary(r, norb) if both else None
+    out = ffx.apply_orbital_rotation(v, U, norb, nelec, U_b=U_b)
+    ref = og.apply_orbital_rotation(_ref(v), U, norb, nelec, U_b=U_b)
+    assert np.max(np.abs(_ref(out) - ref)) <= TOL[torch.complex128]
