@@ -1115,7 +1115,8 @@ void prepare_one_body(ffx_plan_s& P, const double* h, HamAction& A) {
     for (int sp = 0; sp < 2; ++sp)
       est += 1.0 + (N > 1 ? P.n[sp] * (offdiag / N) * (double)(N - P.n[sp]) / (N - 1) : 0.0);
     if (forced || est <= 64.0) {
-      for (int sp = 0; sp < 2; ++sp) t[sp] = build_one_body_table(N, P.str[sp], hv);
+      t[0] = build_one_body_table(N, P.str[0], hv);
+      t[1] = P.n[1] == P.n[0] ? t[0] : build_one_body_table(N, P.str[1], hv);
       const double per = (double)t[0].src.size() / (double)P.dim[0] + (double)t[1].src.size() / (double)P.dim[1];
       direct = forced || per <= 48.0;
     }

@@ -4,7 +4,6 @@
 #include <algorithm>
 #include <cmath>
 #include <map>
-#include <unordered_map>
 
 #include "ffx.h"
 
@@ -16,6 +15,27 @@ int64_t binom(int n, int k) {
   for (int i = 0; i < k; ++i) r = r * (n - i) / (i + 1);
   return r;
 }
+
+namespace {
+struct BinomialTable {
+  int64_t c[33][34];  // up to 32 orbitals
+  BinomialTable() {
+    for (int n = 0; n <= 32; ++n)
+      for (int k = 0; k <= 33; ++k) c[n][k] = binom(n, k);
+  }
+};
+const BinomialTable& binomials() {
+  static const BinomialTable t;
+  return t;
+}
+// index of a configuration among the ascending ones with its electron number
+int64_t colex_rank(uint64_t S) {
+  const BinomialTable& bin = binomials();
+  int64_t r = 0;
+  for (int i = 1; S; S &= S - 1, ++i) r += bin.c[__builtin_ctzll(S)][i];
+  return r;
+}
+}  // namespace
 
 std::vector<uint64_t> make_strings(int norb, int n) {
   std::vector<uint64_t> out;
@@ -656,9 +676,6 @@ std::vector<cd> dagger(int n, const std::vector<cd>& A) {
 
 OneBodyTable build_one_body_table(int norb, const std::vector<uint64_t>& strs, const std::vector<double>& h) {
   OneBodyTable t;
-  std::unordered_map<uint64_t, int32_t> addr;
-  addr.reserve(strs.size() * 2);
-  for (size_t i = 0; i < strs.size(); ++i) addr[strs[i]] = (int32_t)i;
   t.off.reserve(strs.size() + 1);
   t.off.push_back(0);
   for (size_t j = 0; j < strs.size(); ++j) {
@@ -681,9 +698,7 @@ OneBodyTable build_one_body_table(int norb, const std::vector<uint64_t>& strs, c
         const int lo = std::min(p, q), hi = std::max(p, q);
         const uint64_t between = ((1ull << hi) - 1) & ~((1ull << (lo + 1)) - 1);
         const double sign = (__builtin_popcountll(I & between) & 1) ? -1.0 : 1.0;
-        auto it = addr.find(I);
-        if (it == addr.end()) throw Error(FFX_EDEVICE, "one-body table: configuration not in the sector");
-        t.src.push_back(it->second);
+        t.src.push_back((int32_t)colex_rank(I));
         t.coef.push_back(sign * hv);
       }
     }
@@ -788,26 +803,41 @@ std::vector<cd> expm_antihermitian(int n, const std::vector<cd>& K) {
 
 std::vector<cd> slater_column_minors(int norb, int n, const std::vector<cd>& U,
                                      const std::vector<uint64_t>& strs) {
-  // level m: D_m(S) = det U[S, 0:m] over m-subsets S, expanded along column m-1
-  std::unordered_map<uint64_t, cd> prev, cur;
-  prev[0] = 1.0;
+  // level m: D_m(S) = det U[S, 0:m] over m-subsets S in ascending order (by
+  // colex rank), expanded along column m-1.  S without its i-th orbital keeps
+  // the rank terms below it, and those above move one place down.
+  const BinomialTable& bin = binomials();
+  std::vector<cd> prev{cd(1.0, 0.0)}, cur;
   for (int m = 1; m <= n; ++m) {
-    cur.clear();
-    for (uint64_t S : make_strings(norb, m)) {
-      cd acc = 0;
+    cur.resize((size_t)bin.c[norb][m]);
+    int orb[64];
+    for (int i = 0; i < m; ++i) orb[i] = i;
+    for (size_t at = 0; at < cur.size(); ++at) {
+      double re = 0.0, im = 0.0;
+      int64_t rank = 0;  // of S without orb[0]
+      for (int i = 1; i < m; ++i) rank += bin.c[orb[i]][i];
+      for (int i = 0; i < m; ++i) {
+        const cd& u = U[orb[i] * norb + (m - 1)];
+        const double sign = ((i + m - 1) & 1) ? -1.0 : 1.0;
+        const double ur = sign * u.real(), ui = sign * u.imag();
+        const cd& d = prev[(size_t)rank];
+        re += ur * d.real() - ui * d.imag();
+        im += ur * d.imag() + ui * d.real();
+        if (i + 1 < m) rank += bin.c[orb[i]][i + 1] - bin.c[orb[i + 1]][i + 1];
+      }
+      cur[at] = cd(re, im);
+      // the next m-subset: the lowest orbital with room above moves up, those below start over
       int i = 0;
-      for (int r = 0; r < norb; ++r) {
-        if (!((S >> r) & 1)) continue;
-        double sign = ((i + m - 1) & 1) ? -1.0 : 1.0;
-        acc += sign * U[r * norb + (m - 1)] * prev[S & ~(1ull << r)];
+      while (i + 1 < m && orb[i] + 1 == orb[i + 1]) {
+        orb[i] = i;
         ++i;
       }
-      cur[S] = acc;
+      ++orb[i];
     }
     prev.swap(cur);
   }
   std::vector<cd> out(strs.size());
-  for (size_t i = 0; i < strs.size(); ++i) out[i] = prev[strs[i]];
+  for (size_t i = 0; i < strs.size(); ++i) out[i] = prev[(size_t)colex_rank(strs[i])];
   return out;
 }
 
