@@ -151,22 +151,29 @@ void build_tables(ffx_batch_s& b) {
       R = (int)std::min<int64_t>({(int64_t)R, (int64_t)64, std::max<int64_t>(nrows, 1)});
       t.rows_per_task[cs] = R;
       b.wq_rows = std::max(b.wq_rows, R);
+      // real rotations work on parts of amplitudes (split_seg_window), complex
+      // ones on amplitudes, of complex64 by 32-bit member offsets
       std::vector<dev::SegWinDev> wins, wins_real;
-      std::vector<uint16_t> mt_real;
-      std::vector<int> mt_wide;  // 32-bit offsets: complex rotations of complex64
+      std::vector<uint16_t> mt_real, mt_cplx;
+      std::vector<int> mt_wide;
+      auto window = [&](const SegWindowTable& t, const std::vector<int>& code) {
+        dev::SegWinDev wd{};
+        wd.chunk_m = b.upload_table(t.chunk_m);
+        wd.n_chunks = (int)t.chunk_m.size();
+        wd.code = b.upload_table(code);
+        return wd;
+      };
       for (int a = 0; ss.Wseg >= 2 && a + ss.Wseg <= ss.wt; ++a) {
         const SegWindowTable one = build_seg_window(P.str[cs], ss.wt, a, ss.Wseg);
         const SegWindowTable rep = replicate_seg_window(one, ss.Wseg, R, (int)len);
-        dev::SegWinDev wd{};
-        wd.chunk_m = b.upload_table(rep.chunk_m);
-        wd.n_chunks = (int)rep.chunk_m.size();
-        wd.code = b.upload_table(pack_class_codes(compact_members(rep, ss.Wseg, mt_real), 0));
-        wins_real.push_back(wd);
+        const SegWindowTable parts = split_seg_window(rep, ss.Wseg);
+        wins_real.push_back(window(parts, pack_class_codes(compact_members(parts, ss.Wseg, mt_real), 0)));
         if (b.c64) {
-          wd.code = b.upload_table(pack_class_codes(rep, (int)mt_wide.size()));
+          wins.push_back(window(rep, pack_class_codes(rep, (int)mt_wide.size())));
           mt_wide.insert(mt_wide.end(), rep.mt.begin(), rep.mt.end());
           while (mt_wide.size() % 4) mt_wide.push_back(0);
-          wins.push_back(wd);
+        } else {
+          wins.push_back(window(rep, pack_class_codes(compact_members(rep, ss.Wseg, mt_cplx), 0)));
         }
       }
       // the strings of one electron fewer and their one-orbital completions
@@ -196,9 +203,9 @@ void build_tables(ffx_batch_s& b) {
       t.win_real[cs] = b.upload_table(wins_real);
       t.mt_real[cs] = (const int4*)b.upload_table(mt_real);
       t.n_mt_real[cs] = (int)mt_real.size() / 8;
-      t.win[cs] = b.c64 ? b.upload_table(wins) : t.win_real[cs];
-      t.mt_all[cs] = b.c64 ? (const int4*)b.upload_table(mt_wide) : t.mt_real[cs];
-      t.n_mt_all[cs] = b.c64 ? (int)mt_wide.size() / 4 : t.n_mt_real[cs];
+      t.win[cs] = b.upload_table(wins);
+      t.mt_all[cs] = (const int4*)(b.c64 ? (const void*)b.upload_table(mt_wide) : (const void*)b.upload_table(mt_cplx));
+      t.n_mt_all[cs] = b.c64 ? (int)mt_wide.size() / 4 : (int)mt_cplx.size() / 8;
       b.max_mt = std::max({b.max_mt, t.n_mt_all[cs], t.n_mt_real[cs]});
       // a segment task holds R rows; a transition-matrix task holds rdm_rows(R) rows of two states
       const size_t rows_held = std::max<size_t>((size_t)R, 2 * (size_t)rdm_rows(R));
@@ -580,7 +587,9 @@ void run_batch(ffx_batch_s& b, const ffx_lucj* ops, const ffx_df_ham* hams, doub
     for (int i : order)
       if (lv < ip[i].p.size()) lvl.push_back(ip[i].p[lv]);
     std::stable_sort(lvl.begin(), lvl.end(),
-                     [](const dev::BPassDev& a, const dev::BPassDev& c) { return a.kind < c.kind; });
+                     [](const dev::BPassDev& a, const dev::BPassDev& c) {
+                       return std::make_pair(a.kind, a.real) < std::make_pair(c.kind, c.real);
+                     });
     for (dev::BPassDev p : lvl) {
       p.first = first;
       first += p.n_tasks;
@@ -650,11 +659,21 @@ void run_batch(ffx_batch_s& b, const ffx_lucj* ops, const ffx_df_ham* hams, doub
     for (size_t lv = 0; lv + 1 < level_start.size(); ++lv) {
       for (int p0 = level_start[lv]; p0 < level_start[lv + 1];) {
         int p1 = p0 + 1;
-        while (p1 < level_start[lv + 1] && all[p1].kind == all[p0].kind) ++p1;
+        while (p1 < level_start[lv + 1] && all[p1].kind == all[p0].kind && all[p1].real == all[p0].real) ++p1;
         const int64_t tasks = (p1 < (int)all.size() ? all[p1].first : first) - all[p0].first;
         if (tasks > 0) {
-          dev::batch_launch_kind(b.c64, all[p0].kind, bd, p0, p1, tasks,
-                                 dev::batch_lds_for(all[p0].kind, b.lds_row_bytes, b.max_mt, b.wq_rows), s);
+          size_t lds = 0;
+          if (all[p0].kind == dev::BK_SEG) {
+            for (int pi = p0; pi < p1; ++pi) {
+              const dev::BTypeDev& t = b.htypes[all[pi].type];
+              const int cs = all[pi].layout == 0 ? 1 : 0;
+              lds = std::max(lds, dev::batch_seg_lds(b.c64, t.rows_per_task[cs], t.dim[cs],
+                                                     all[pi].real ? t.n_mt_real[cs] : t.n_mt_all[cs]));
+            }
+          } else {
+            lds = dev::batch_lds_for(all[p0].kind, b.lds_row_bytes, b.max_mt, b.wq_rows);
+          }
+          dev::batch_launch_kind(b.c64, all[p0].kind, all[p0].real != 0, bd, p0, p1, tasks, lds, s);
           check_launch();
           ++launches;
         }

@@ -35,6 +35,7 @@ namespace ffx {
 namespace dev {
 
 constexpr int kBatchThreads = 256;
+constexpr int kBatchSegThreads = 512;  // segment tasks, one launch per kind
 typedef double bdouble4 __attribute__((ext_vector_type(4)));
 typedef double bdouble2 __attribute__((ext_vector_type(2)));
 typedef float bfloat2 __attribute__((ext_vector_type(2)));
@@ -88,6 +89,17 @@ __device__ __forceinline__ BatchLds batch_lds_map(char* smem, const BatchDev& B,
   return L;
 }
 
+// LDS of one segment task, laid out by its own rows and tables (a launch of
+// segment tasks takes its largest task's)
+__host__ __device__ inline int seg_rows_bytes(int elem, int rows, int64_t len) {
+  return (int)(((int64_t)rows * len * elem + 15) & ~(int64_t)15);
+}
+
+size_t batch_seg_lds(bool c64, int rows, int64_t len, int n_mt) {
+  return (size_t)seg_rows_bytes(c64 ? 8 : 16, rows, len) + (size_t)n_mt * 16 +
+         (kRedDoubles + seg_tab_doubles(rows)) * 8;
+}
+
 size_t batch_lds(bool c64, int lds_row_bytes, int max_mt, int wq_rows) {
   (void)c64;
   return batch_lds_kind(-1, lds_row_bytes, max_mt, wq_rows);
@@ -97,7 +109,7 @@ size_t batch_lds_for(int kind, int lds_row_bytes, int max_mt, int wq_rows) {
   return batch_lds_kind(kind, lds_row_bytes, max_mt, wq_rows);
 }
 
-// fixed-order block sum (4 waves); every thread gets the result
+// fixed-order block sum (up to 16 waves); every thread gets the result
 __device__ __forceinline__ double batch_block_sum(double v, double* red) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   const int w = threadIdx.x >> 6;
@@ -423,66 +435,99 @@ __device__ __forceinline__ void dgrad_task(const BPassDev& ps, const BTypeDev& t
 // ---------------------------------------------------------------------------
 // segment pass on a block of rows (or columns) held back to back in LDS
 // ---------------------------------------------------------------------------
-template <int W, bool REAL, class R>
-__device__ __forceinline__ void seg_task(const BatchDev& B, const BPassDev& ps, const BTypeDev& ty, int task, const BatchLds& L) {
-  using V = typename V2T<R>::type;
-  const int cs = ps.layout == 0 ? 1 : 0, rs = 1 - cs;
-  const int N = ty.norb;
-  const int64_t nrows = pick2(ty.dim, rs), len = pick2(ty.dim, cs), ncols_state = ty.dim[1];
-  const int RR = pick2(ty.rows_per_task, cs);
-  const void* src = ps.src;
-  void* dst = ps.dst;
-  if (task >= ps.half) {
-    task -= ps.half;
-    src = ps.src2;
-    dst = ps.dst2;
+// x / d for x d < 2^32 by a multiplication with ceil(2^32 / d)
+struct FastDiv {
+  uint32_t d, m;
+  __device__ __forceinline__ explicit FastDiv(uint32_t by) : d(by), m(0xFFFFFFFFu / by + 1) {}
+  __device__ __forceinline__ uint32_t quot(uint32_t x) const { return d == 1 ? x : __umulhi(x, m); }
+};
+
+// Where a segment task works, from its descriptors.  The descriptors are read
+// again (scalar loads) by each part of the task that needs them: held across
+// the Givens stages they cost 180 spilled scalar registers.
+template <class T>
+__device__ __forceinline__ T read_again(const T* p) {
+  const uint64_t v = (uint64_t)(uintptr_t)p;
+  uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  asm volatile("" : "+s"(lo), "+s"(hi));
+  return uniform_load((const T*)(uintptr_t)(((uint64_t)hi << 32) | lo));
+}
+
+template <class V>
+struct SegTask {
+  int layout, cs, N, RR, nr, ne;
+  unsigned len;
+  int64_t r0, ncols_state;
+  const V* src;
+  V* dst;
+  __device__ __forceinline__ SegTask(const BPassDev& ps, const BTypeDev& ty, int task) {
+    layout = ps.layout;
+    cs = layout == 0 ? 1 : 0;
+    N = ty.norb;
+    RR = pick2(ty.rows_per_task, cs);
+    len = (unsigned)pick2(ty.dim, cs);
+    ncols_state = ty.dim[1];
+    const bool second = task >= ps.half;
+    src = (const V*)(second ? ps.src2 : ps.src);
+    dst = (V*)(second ? ps.dst2 : ps.dst);
+    r0 = (int64_t)(second ? task - ps.half : task) * RR;
+    nr = (int)std::min<int64_t>(RR, pick2(ty.dim, 1 - cs) - r0);
+    ne = nr * (int)len;
   }
-  const int64_t r0 = (int64_t)task * RR;
-  const int nr = (int)std::min<int64_t>(RR, nrows - r0);
-  const int64_t nel = (int64_t)nr * len;
+};
+
+template <int W, bool REAL, class R>
+__device__ __forceinline__ void seg_task(const BPassDev* pp, const BTypeDev* pt, int task, const BatchLds& L) {
+  using V = typename V2T<R>::type;
   const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, nwaves = nthr >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform in the wave: chunk loops stay scalar
   V* buf = (V*)L.rows;
-  const V* s = (const V*)src;
-
-  // gather: element (r, k) of the layout lands at buf[r * len + k]; every
-  // thread requests kU elements before it stores any.  A task holds at most
-  // 64 rows of at most 924 amplitudes, so element indexes and their quotients
-  // by the row count are taken in 32-bit unsigned arithmetic.
-  constexpr int kU = 8;
-  const int ne = (int)nel;
-  const unsigned unr = (unsigned)nr, ulen = (unsigned)len;
-  for (int x0 = tid; x0 < ne; x0 += kU * nthr) {
-    V t[kU];
+  double acc = 0.0;
+  const StageDev* stages;
+  const SegWinDev* wins;
+  int n_stages;
+  {
+    const BPassDev ps = uniform_load(pp);
+    const BTypeDev ty = uniform_load(pt);
+    const SegTask<V> k(ps, ty, task);
+    stages = ps.stages;
+    n_stages = ps.n_stages;
+    wins = REAL ? pick2(ty.win_real, k.cs) : pick2(ty.win, k.cs);
+    // gather: element (r, c) of the layout lands at buf[r * len + c]; every
+    // thread requests kU elements before it stores any
+    constexpr int kU = 8;
+    const FastDiv by_nr((unsigned)k.nr);
+    for (int x0 = tid; x0 < k.ne; x0 += kU * nthr) {
+      V t[kU];
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const unsigned x = (unsigned)min(x0 + u * nthr, ne - 1);
-      if (ps.layout == 0) {
-        t[u] = s[r0 * len + x];
-      } else {
-        const unsigned k = x / unr, r = x - k * unr;
-        t[u] = s[(int64_t)k * ncols_state + r0 + r];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) keep(t[u]);
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int x = x0 + u * nthr;
-      if (x < ne) {
-        if (ps.layout == 0) {
-          buf[x] = t[u];
+      for (int u = 0; u < kU; ++u) {
+        const unsigned x = (unsigned)min(x0 + u * nthr, k.ne - 1);
+        if (k.layout == 0) {
+          t[u] = k.src[k.r0 * k.len + x];
         } else {
-          const unsigned k = (unsigned)x / unr, r = (unsigned)x - k * unr;
-          buf[r * ulen + k] = t[u];
+          const unsigned c = by_nr.quot(x), r = x - c * (unsigned)k.nr;
+          t[u] = k.src[(int64_t)c * k.ncols_state + k.r0 + r];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) keep(t[u]);
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int x = x0 + u * nthr;
+        if (x < k.ne) {
+          if (k.layout == 0) {
+            buf[x] = t[u];
+          } else {
+            const unsigned c = by_nr.quot((unsigned)x), r = (unsigned)x - c * (unsigned)k.nr;
+            buf[r * k.len + c] = t[u];
+          }
         }
       }
     }
-  }
-  for (int64_t x = nel + tid; x < (int64_t)RR * len; x += nthr) buf[x] = V{};
-  {
-    const int n4 = REAL ? pick2(ty.n_mt_real, cs) : pick2(ty.n_mt_all, cs);
-    const int4* m4 = REAL ? pick2(ty.mt_real, cs) : pick2(ty.mt_all, cs);
+    for (int x = k.ne + tid; x < k.RR * (int)k.len; x += nthr) buf[x] = V{};
+    const int n4 = REAL ? pick2(ty.n_mt_real, k.cs) : pick2(ty.n_mt_all, k.cs);
+    const int4* m4 = REAL ? pick2(ty.mt_real, k.cs) : pick2(ty.mt_all, k.cs);
     for (int i0 = tid; i0 < n4; i0 += 4 * nthr) {
       int4 q[4];
 #pragma unroll
@@ -496,34 +541,37 @@ __device__ __forceinline__ void seg_task(const BatchDev& B, const BPassDev& ps, 
   }
   __syncthreads();
 
-  const uint32_t* cmask = pick2(ty.masks, cs);
-  const uint32_t* rmask = pick2(ty.masks, rs) + r0;
-  double acc = 0.0;
   // each Givens stage's rotations and first class codes are requested a stage
   // ahead (as in the segment pass)
-  const SegWinDev* wins = REAL ? pick2(ty.win_real, cs) : pick2(ty.win, cs);
   RotLane<R> rl_next{nullptr};
   ChunkAhead fc_next{1, 1, -1, -1};
   auto fetch = [&](int si) {
-    const StageDev st = uniform_load(ps.stages + si);
+    const StageDev st = uniform_load(stages + si);
     if (st.type == ST_GIVENS) {
       rl_next = fetch_rot_lane<R>(st.rots);
       fc_next = fetch_first_chunk(uniform_load(wins + st.a), wave, lane, nwaves);
     }
   };
-  if (ps.n_stages > 0) fetch(0);
-  for (int si = 0; si < ps.n_stages; ++si) {
-    const StageDev st = uniform_load(ps.stages + si);
+  if (n_stages > 0) fetch(0);
+  for (int si = 0; si < n_stages; ++si) {
+    const StageDev st = uniform_load(stages + si);
     const RotLane<R> rl = rl_next;
     const ChunkAhead fc = fc_next;
-    if (si + 1 < ps.n_stages) fetch(si + 1);
+    if (si + 1 < n_stages) fetch(si + 1);
     if (st.type == ST_GIVENS) {
       const SegWinDev wt = uniform_load(wins + st.a);
-      givens_stage<W, REAL, R>(st.shape, buf, (const char*)L.mt, wt, rl, st.nrot, wave, nwaves, lane, fc);
+      givens_stage<W, REAL, R, REAL>(st.shape, buf, (const char*)L.mt, wt, rl, st.nrot, wave, nwaves, lane, fc);
     } else {
+      const BPassDev ps = read_again(pp);
+      const BTypeDev ty = read_again(pt);
+      const SegTask<V> k(ps, ty, task);
+      const int N = k.N;
+      const uint32_t* cmask = pick2(ty.masks, k.cs);
+      const uint32_t* rmask = pick2(ty.masks, 1 - k.cs) + k.r0;
+      const FastDiv by_N((unsigned)N), by_len(k.len);
       // per row: cross weights w_r[q] = sum_{p in row} C[p][q] and the row factor
-      for (int i = tid; i < nr * N; i += nthr) {
-        const int r = i / N, q = i - r * N;
+      for (int i = tid; i < k.nr * N; i += nthr) {
+        const int r = (int)by_N.quot((unsigned)i), q = i - r * N;
         double w = 0.0;
         if (st.C) {
           // the column of C is requested whole before the masked sum
@@ -537,9 +585,9 @@ __device__ __forceinline__ void seg_task(const BatchDev& B, const BPassDev& ps, 
         }
         L.wq[r * kBatchMaxOrb + q] = w;
       }
-      for (int r = tid; r < nr; r += nthr) {
+      for (int r = tid; r < k.nr; r += nthr) {
         const uint32_t rm = rmask[r];
-        const double arow = st.A ? st.A[r0 + r] : 0.0;
+        const double arow = st.A ? st.A[k.r0 + r] : 0.0;
         if (st.type == ST_PHASE) {
           double g = st.scale * arow;
           if (st.drow)
@@ -557,16 +605,16 @@ __device__ __forceinline__ void seg_task(const BatchDev& B, const BPassDev& ps, 
       }
       __syncthreads();
       const bool cross = st.C != nullptr;
-      for (int x = tid; x < ne; x += nthr) {
-        const unsigned r = (unsigned)x / ulen, k = (unsigned)x - r * ulen;
+      for (int x = tid; x < k.ne; x += nthr) {
+        const unsigned r = by_len.quot((unsigned)x), c = (unsigned)x - r * k.len;
         double cr = 0.0;
         if (cross)
-          for (uint32_t b = cmask[k]; b; b &= b - 1) cr += L.wq[r * kBatchMaxOrb + __builtin_ctz(b)];
+          for (uint32_t b = cmask[c]; b; b &= b - 1) cr += L.wq[r * kBatchMaxOrb + __builtin_ctz(b)];
         V y = buf[x];
         if (st.type == ST_PHASE) {
           zc128 f{L.rowf[2 * r], L.rowf[2 * r + 1]};
-          if (st.colf) f = zmul(f, ((const zc128*)st.colf)[k]);
-          if (__builtin_popcount(cmask[k] & st.sign_col) & 1) {
+          if (st.colf) f = zmul(f, ((const zc128*)st.colf)[c]);
+          if (__builtin_popcount(cmask[c] & st.sign_col) & 1) {
             f.x = -f.x;
             f.y = -f.y;
           }
@@ -579,7 +627,7 @@ __device__ __forceinline__ void seg_task(const BatchDev& B, const BPassDev& ps, 
           o.y = (R)((double)y.x * f.y + (double)y.y * f.x);
           buf[x] = o;
         } else {
-          const double f = L.rowf[2 * r] + (st.B ? st.B[k] : 0.0) + cr;
+          const double f = L.rowf[2 * r] + (st.B ? st.B[c] : 0.0) + cr;
           if (st.type == ST_SCALE) {
             y.x = (R)(f * (double)y.x);
             y.y = (R)(f * (double)y.y);
@@ -593,42 +641,36 @@ __device__ __forceinline__ void seg_task(const BatchDev& B, const BPassDev& ps, 
     __syncthreads();
   }
 
-  if (ps.mode != SEG_NONE) {
-    V* d = (V*)dst;
-    const bool add = ps.mode == SEG_ACCUM;
-    if (ps.layout == 0) {
-      for (int x = tid; x < ne; x += nthr) {
-        V v = buf[x];
+  {
+    const BPassDev ps = read_again(pp);
+    const SegTask<V> k(ps, read_again(pt), task);
+    if (ps.mode != SEG_NONE) {
+      const bool add = ps.mode == SEG_ACCUM;
+      const FastDiv by_nr((unsigned)k.nr);
+      for (int x = tid; x < k.ne; x += nthr) {
+        int64_t at = k.r0 * k.len + x;
+        unsigned e = (unsigned)x;
+        if (k.layout != 0) {
+          const unsigned c = by_nr.quot((unsigned)x), r = (unsigned)x - c * (unsigned)k.nr;
+          at = (int64_t)c * k.ncols_state + k.r0 + r;
+          e = r * k.len + c;
+        }
+        V v = buf[e];
         if (add) {
-          const V a = d[r0 * len + x];
+          const V a = k.dst[at];
           v.x += a.x;
           v.y += a.y;
         }
-        d[r0 * len + x] = v;
-      }
-    } else {
-      for (int x = tid; x < ne; x += nthr) {
-        const unsigned k = (unsigned)x / unr, r = (unsigned)x - k * unr;
-        const int64_t gi = (int64_t)k * ncols_state + r0 + r;
-        V v = buf[r * ulen + k];
-        if (add) {
-          const V a = d[gi];
-          v.x += a.x;
-          v.y += a.y;
-        }
-        d[gi] = v;
+        k.dst[at] = v;
       }
     }
-  }
-  if (ps.partials) {
-    const double t = batch_block_sum(acc, L.red);
-    if (tid == 0) ps.partials[task] = t;
+    if (ps.partials) {
+      const double t = batch_block_sum(acc, L.red);
+      if (tid == 0) ps.partials[task - (task >= ps.half ? ps.half : 0)] = t;
+    }
   }
 }
 
-// ---------------------------------------------------------------------------
-// the persistent kernel
-// ---------------------------------------------------------------------------
 template <int W, class R>
 __global__ __launch_bounds__(kBatchThreads) void k_batch(BatchDev B) {
   extern __shared__ __align__(16) char smem[];
@@ -690,9 +732,9 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch(BatchDev B) {
       case BK_OUTER: outer_task<R>(ps, ty, task); break;
       case BK_SEG:
         if (ps.real)
-          seg_task<W, true, R>(B, ps, ty, task, L);
+          seg_task<W, true, R>(B.passes + pi, B.types + ps.type, task, L);
         else
-          seg_task<W, false, R>(B, ps, ty, task, L);
+          seg_task<W, false, R>(B.passes + pi, B.types + ps.type, task, L);
         break;
       case BK_INNER: inner_task<R>(ps, ty, task, L.red); break;
       case BK_RDM: rdm_task<R>(ps, ty, task, L); break;
@@ -708,16 +750,36 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch(BatchDev B) {
 }
 
 // Level-synchronous form: one launch runs the passes [p0, p1) of one level
-// that all have kind KIND (the host groups a level's passes by kind), one block
-// per task; ordering between levels comes from the launches.  Each launch
-// carries only its kind's code, so its register count, and with it the number
-// of blocks a compute unit holds, is that kind's own rather than the largest of
-// all (segment tasks: 126 registers for complex64 instead of 196).
-template <int W, class R, int KIND>
-__global__ __launch_bounds__(kBatchThreads) void k_batch_kind(BatchDev B, int p0, int p1) {
+// that all have kind KIND (the host groups a level's passes by kind, segment
+// passes also by real and complex rotations), one block per task; ordering
+// between levels comes from the launches.  Each launch carries only its kind's
+// code, so its register count, and with it the number of blocks a compute unit
+// holds, is that kind's own.  Segment tasks take 8 waves and lay LDS out by
+// their own rows and tables: three blocks to a compute unit at complex64
+// instead of two of 4 waves.  64 sectors of 8 to 12 orbitals in complex64, a
+// launch of one real rotation pass each: 333 us before, 299 us so, 275 us with
+// the runs of tasks per XCD (gathers and stores alone take half of it).
+constexpr int kind_threads(int kind) { return kind == BK_SEG ? kBatchSegThreads : kBatchThreads; }
+// waves per SIMD that the registers must leave: three blocks of 8 waves, for 13
+// spilled registers of the real complex64 passes (2 % faster than two blocks
+// without; the others would spill 59 and more, and run slower)
+constexpr int kind_waves(int kind, bool real, size_t real_bytes) {
+  return kind == BK_SEG && real && real_bytes == 4 ? 6 : 1;
+}
+
+template <int W, class R, int KIND, bool REAL = false>
+__global__ __launch_bounds__(kind_threads(KIND), kind_waves(KIND, REAL, sizeof(R))) void k_batch_kind(BatchDev B, int p0, int p1) {
   extern __shared__ __align__(16) char smem[];
-  const BatchLds L = batch_lds_map(smem, B, KIND);
-  const int64_t t = B.passes[p0].first + (int64_t)blockIdx.x;
+  // Blocks are dealt to the 8 XCDs in turn; a run of kXcdRun tasks goes to one
+  // of them, so that the few columns each task gathers from a line of 16
+  // amplitudes come from one L2 (4 rows of 924 strings: 32 bytes of 128).
+  constexpr unsigned kXcdRun = 16;
+  unsigned blk = blockIdx.x;
+  if (blk < gridDim.x / (8 * kXcdRun) * (8 * kXcdRun)) {
+    const unsigned i = blk % (8 * kXcdRun);
+    blk = blk - i + (i & 7) * kXcdRun + (i >> 3);
+  }
+  const int64_t t = B.passes[p0].first + (int64_t)blk;
   int lo = p0, hi = p1 - 1;  // last pass of the group whose first task <= t
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -737,14 +799,19 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch_kind(BatchDev B, int p0
   if constexpr (KIND == BK_TABLES) tables_task(ps, ty, task);
   if constexpr (KIND == BK_OUTER) outer_task<R>(ps, ty, task);
   if constexpr (KIND == BK_SEG) {
-    if (ps.real)
-      seg_task<W, true, R>(B, ps, ty, task, L);
-    else
-      seg_task<W, false, R>(B, ps, ty, task, L);
+    const int cs = ps.layout == 0 ? 1 : 0;
+    const int RR = pick2(ty.rows_per_task, cs);
+    BatchLds L{};
+    L.rows = smem;
+    L.mt = (int4*)(smem + seg_rows_bytes((int)sizeof(typename V2T<R>::type), RR, pick2(ty.dim, cs)));
+    L.wq = (double*)(L.mt + (REAL ? pick2(ty.n_mt_real, cs) : pick2(ty.n_mt_all, cs)));
+    L.rowf = L.wq + RR * kBatchMaxOrb;
+    L.red = L.rowf + 2 * RR;
+    seg_task<W, REAL, R>(B.passes + lo, B.types + ps.type, task, L);
   }
-  if constexpr (KIND == BK_INNER) inner_task<R>(ps, ty, task, L.red);
-  if constexpr (KIND == BK_RDM) rdm_task<R>(ps, ty, task, L);
-  if constexpr (KIND == BK_DGRAD) dgrad_task<R>(ps, ty, task, L.acc);
+  if constexpr (KIND == BK_INNER) inner_task<R>(ps, ty, task, batch_lds_map(smem, B, KIND).red);
+  if constexpr (KIND == BK_RDM) rdm_task<R>(ps, ty, task, batch_lds_map(smem, B, KIND));
+  if constexpr (KIND == BK_DGRAD) dgrad_task<R>(ps, ty, task, batch_lds_map(smem, B, KIND).acc);
   if constexpr (KIND == BK_SUM) sum_task(ps);
 }
 
@@ -790,9 +857,9 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch_coop(BatchDev B, const 
             case BK_OUTER: outer_task<R>(ps, ty, task); break;
             case BK_SEG:
               if (ps.real)
-                seg_task<W, true, R>(B, ps, ty, task, L);
+                seg_task<W, true, R>(B.passes + lo, B.types + ps.type, task, L);
               else
-                seg_task<W, false, R>(B, ps, ty, task, L);
+                seg_task<W, false, R>(B.passes + lo, B.types + ps.type, task, L);
               break;
             case BK_INNER: inner_task<R>(ps, ty, task, L.red); break;
             case BK_RDM: rdm_task<R>(ps, ty, task, L); break;
@@ -846,24 +913,29 @@ hipError_t batch_launch_coop(bool c64, const BatchDev& b, const int* level_start
              : launch_coop<6, double>(b, level_start, n_levels, level_ctr, blocks, lds, s);
 }
 
-template <int W, class R, int KIND>
+template <int W, class R, int KIND, bool REAL = false>
 static void launch_kind(const BatchDev& b, int p0, int p1, int64_t tasks, size_t lds, hipStream_t s) {
-  auto k = k_batch_kind<W, R, KIND>;
+  auto k = k_batch_kind<W, R, KIND, REAL>;
   static bool attr_set = false;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, kBatchMaxDynLds);
     (void)hipGetLastError();
     attr_set = true;
   }
-  hipLaunchKernelGGL(k, dim3((unsigned)tasks), dim3(kBatchThreads), lds, s, b, p0, p1);
+  hipLaunchKernelGGL(k, dim3((unsigned)tasks), dim3(kind_threads(KIND)), lds, s, b, p0, p1);
 }
 
 template <class R>
-static void launch_kind_r(int kind, const BatchDev& b, int p0, int p1, int64_t tasks, size_t lds, hipStream_t s) {
+static void launch_kind_r(int kind, bool real, const BatchDev& b, int p0, int p1, int64_t tasks, size_t lds, hipStream_t s) {
   switch (kind) {
     case BK_TABLES: launch_kind<6, R, BK_TABLES>(b, p0, p1, tasks, lds, s); break;
     case BK_OUTER: launch_kind<6, R, BK_OUTER>(b, p0, p1, tasks, lds, s); break;
-    case BK_SEG: launch_kind<6, R, BK_SEG>(b, p0, p1, tasks, lds, s); break;
+    case BK_SEG:
+      if (real)
+        launch_kind<6, R, BK_SEG, true>(b, p0, p1, tasks, lds, s);
+      else
+        launch_kind<6, R, BK_SEG, false>(b, p0, p1, tasks, lds, s);
+      break;
     case BK_INNER: launch_kind<6, R, BK_INNER>(b, p0, p1, tasks, lds, s); break;
     case BK_RDM: launch_kind<6, R, BK_RDM>(b, p0, p1, tasks, lds, s); break;
     case BK_DGRAD: launch_kind<6, R, BK_DGRAD>(b, p0, p1, tasks, lds, s); break;
@@ -872,12 +944,12 @@ static void launch_kind_r(int kind, const BatchDev& b, int p0, int p1, int64_t t
   }
 }
 
-void batch_launch_kind(bool c64, int kind, const BatchDev& b, int p0, int p1, int64_t tasks, size_t lds,
+void batch_launch_kind(bool c64, int kind, bool real, const BatchDev& b, int p0, int p1, int64_t tasks, size_t lds,
                        hipStream_t s) {
   if (c64)
-    launch_kind_r<float>(kind, b, p0, p1, tasks, lds, s);
+    launch_kind_r<float>(kind, real, b, p0, p1, tasks, lds, s);
   else
-    launch_kind_r<double>(kind, b, p0, p1, tasks, lds, s);
+    launch_kind_r<double>(kind, real, b, p0, p1, tasks, lds, s);
 }
 
 

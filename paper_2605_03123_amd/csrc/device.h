@@ -466,11 +466,13 @@ struct BatchDev {
 size_t batch_lds(bool c64, int lds_row_bytes, int max_mt, int wq_rows);
 // LDS bytes of a launch that runs tasks of one kind only
 size_t batch_lds_for(int kind, int lds_row_bytes, int max_mt, int wq_rows);
+// of one segment task of `rows` rows of len amplitudes with n_mt 16-byte words of member offsets
+size_t batch_seg_lds(bool c64, int rows, int64_t len, int n_mt);
 int batch_blocks_per_cu(bool c64, int threads, size_t lds);
 void batch_launch(bool c64, const BatchDev& b, int blocks, int threads, size_t lds, hipStream_t s);
 // level-synchronous form: the tasks of passes [p0, p1) (one level), one block each
 // passes [p0, p1) of one level, all of kind `kind`, one block per task
-void batch_launch_kind(bool c64, int kind, const BatchDev& b, int p0, int p1, int64_t tasks, size_t lds,
+void batch_launch_kind(bool c64, int kind, bool real, const BatchDev& b, int p0, int p1, int64_t tasks, size_t lds,
                        hipStream_t s);
 
 // single cooperative launch over all levels (grid barrier between levels); blocks must not exceed

@@ -98,6 +98,23 @@ def test_one_body_tables(ffx, monkeypatch, norb, nelec, dtype):
     assert np.max(np.abs(_ref(out) - ref)) <= TOL[dtype] * max(1.0, float(np.abs(ref).max()))
 
 
+# batched sectors whose tasks hold 64 rows, a few and one; rows of one string; enough tasks for the runs that go to one
+# XCD, and fewer; real and complex rotations.  Against the sector by itself, at the bounds of the batched results.
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+def test_batched_sectors_of_all_row_lengths(ffx, dtype):
+    sectors = [(6, (1, 5)), (6, (6, 2)), (7, (3, 1)), (9, (2, 7)), (12, (1, 6)), (13, (6, 6)), (14, (7, 3))]
+    params, hams = [], []
+    for k, (norb, _) in enumerate(sectors):
+        r = synth.rng([59, k])
+        params.append(synth.lucj_params(r, norb, 1))
+        hams.append(synth.df_hamiltonian(r, norb, 2))
+    e, g = ffx.Batch(sectors, dtype=dtype).lucj_energy_grad(params, hams, 1)
+    for i, (norb, nelec) in enumerate(sectors):
+        e1, g1 = ffx.lucj_energy_grad(params[i], hams[i], norb, nelec, 1, dtype=dtype)
+        assert abs(e[i] - e1) <= TOL[dtype] * max(1.0, abs(e1))
+        assert np.max(np.abs(g[i] - g1)) <= TOL[dtype] * max(1.0, np.max(np.abs(g1)))
+
+
 # rotations in the dense form: sectors below one 16 x 16 tile, with remainders of tile and k step, the largest that
 # take it; electron numbers that share the compound launch, that do not, and 8 of them; more orbitals than the kernel
 # arguments hold; empty spins
