@@ -674,6 +674,16 @@ std::vector<cd> dagger(int n, const std::vector<cd>& A) {
   return B;
 }
 
+OneBodyGrid onebody_grid(int64_t rows, int64_t cols, int elem_bytes) {
+  OneBodyGrid g;
+  g.row_blocks = (rows + 3) / 4;
+  g.tiles = (cols + 63) / 64;
+  // a tile and what streams past it share an XCD's L2; fewer tiles than XCDs would leave some idle
+  g.per_xcd = g.tiles >= 8 && rows * 64 * elem_bytes <= (3 << 20);
+  g.blocks = (g.per_xcd ? (g.tiles + 7) / 8 * 8 : g.tiles) * g.row_blocks;
+  return g;
+}
+
 OneBodyTable build_one_body_table(int norb, const std::vector<uint64_t>& strs, const std::vector<double>& h) {
   OneBodyTable t;
   t.off.reserve(strs.size() + 1);

@@ -196,6 +196,28 @@ struct OneBodyTable {
 };
 OneBodyTable build_one_body_table(int norb, const std::vector<uint64_t>& strs, const std::vector<double>& h);
 
+// The blocks of the one-body row kernel over a rows x cols state: each takes 4
+// rows and a tile of 64 columns.  A launch of blocks of 256 threads must stay
+// below 2^32 work-items (HIP's limit on a grid dimension), which is 2^32
+// amplitudes here, so larger states go out as several launches of at most
+// kOneBodyLaunch blocks; it is a multiple of 8, so that a block's place in the
+// whole grid still names its XCD.
+constexpr int64_t kOneBodyLaunch = (int64_t)1 << 23;
+struct OneBodyGrid {
+  int64_t row_blocks, tiles;
+  bool per_xcd;    // each XCD takes column tiles of its own
+  int64_t blocks;  // of all launches; fewer than 2^32 for any state of up to 32 orbitals
+};
+OneBodyGrid onebody_grid(int64_t rows, int64_t cols, int elem_bytes);
+// what block b of the whole grid takes
+struct OneBodyBlock {
+  uint32_t tile, row_block;
+};
+constexpr OneBodyBlock onebody_block(uint32_t b, uint32_t row_blocks, bool per_xcd) {
+  const uint32_t k = per_xcd ? b >> 3 : b;
+  return OneBodyBlock{per_xcd ? (b & 7) + 8 * (k / row_blocks) : k / row_blocks, k % row_blocks};
+}
+
 // Bessel functions of the first kind J_0(z) .. J_kmax(z), z >= 0, by Miller's
 // backward recurrence J_{k-1} = (2k / z) J_k - J_{k+1} from a start index well
 // above kmax, normalised by J_0 + 2 (J_2 + J_4 + ...) = 1.

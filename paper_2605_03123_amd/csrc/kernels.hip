@@ -24,6 +24,7 @@
 
 #include "dev_common.h"
 #include "device.h"
+#include "host.h"
 
 namespace ffx {
 namespace dev {
@@ -613,15 +614,15 @@ template <class R, bool CHEB>
 __global__ __launch_bounds__(256) void k_onebody_rows(const typename V2T<R>::type* __restrict__ src,
                                                       typename V2T<R>::type* dst,
                                                       const typename V2T<R>::type* add, int64_t rows,
-                                                      int64_t cols, unsigned row_blocks, unsigned tiles, int per_xcd,
-                                                      const int64_t* __restrict__ off,
+                                                      int64_t cols, unsigned block0, unsigned row_blocks,
+                                                      unsigned tiles, int per_xcd, const int64_t* __restrict__ off,
                                                       const int32_t* __restrict__ srow,
                                                       const double* __restrict__ coef, OneBodyDiag dg,
                                                       ChebStep ch) {
   using V = typename V2T<R>::type;
-  const unsigned b = per_xcd ? blockIdx.x >> 3 : blockIdx.x;
-  const unsigned tile = per_xcd ? (blockIdx.x & 7) + 8 * (b / row_blocks) : b / row_blocks;
-  const int64_t j = (int64_t)(b % row_blocks) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const OneBodyBlock ob = onebody_block(block0 + blockIdx.x, row_blocks, per_xcd != 0);
+  const unsigned tile = ob.tile;
+  const int64_t j = (int64_t)ob.row_block * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (tile >= tiles || j >= rows) return;
   const int64_t col = (int64_t)tile * 64 + (threadIdx.x & 63);
   const bool in = col < cols;
@@ -688,16 +689,18 @@ static void onebody_rows_r(const void* src, void* dst, const void* add, int64_t 
                            const int64_t* off, const int32_t* srow, const double* coef, const OneBodyDiag& dg,
                            const ChebStep* ch, hipStream_t s) {
   using V = typename V2T<R>::type;
-  const unsigned row_blocks = (unsigned)((rows + 3) / 4), tiles = (unsigned)((cols + 63) / 64);
-  // a tile and what streams past it share an XCD's L2; fewer tiles than XCDs would leave some idle
-  const bool per_xcd = tiles >= 8 && rows * 64 * (int64_t)sizeof(V) <= (3 << 20);
-  const unsigned blocks = per_xcd ? (tiles + 7) / 8 * 8 * row_blocks : tiles * row_blocks;
-  if (ch)
-    hipLaunchKernelGGL((k_onebody_rows<R, true>), dim3(blocks), dim3(256), 0, s, (const V*)src, (V*)nullptr,
-                       (const V*)add, rows, cols, row_blocks, tiles, (int)per_xcd, off, srow, coef, dg, *ch);
-  else
-    hipLaunchKernelGGL((k_onebody_rows<R, false>), dim3(blocks), dim3(256), 0, s, (const V*)src, (V*)dst,
-                       (const V*)add, rows, cols, row_blocks, tiles, (int)per_xcd, off, srow, coef, dg, ChebStep{});
+  const OneBodyGrid g = onebody_grid(rows, cols, (int)sizeof(V));
+  for (int64_t b0 = 0; b0 < g.blocks; b0 += kOneBodyLaunch) {
+    const dim3 grid((unsigned)std::min(g.blocks - b0, kOneBodyLaunch));
+    if (ch)
+      hipLaunchKernelGGL((k_onebody_rows<R, true>), grid, dim3(256), 0, s, (const V*)src, (V*)nullptr, (const V*)add,
+                         rows, cols, (unsigned)b0, (unsigned)g.row_blocks, (unsigned)g.tiles, (int)g.per_xcd, off,
+                         srow, coef, dg, *ch);
+    else
+      hipLaunchKernelGGL((k_onebody_rows<R, false>), grid, dim3(256), 0, s, (const V*)src, (V*)dst, (const V*)add,
+                         rows, cols, (unsigned)b0, (unsigned)g.row_blocks, (unsigned)g.tiles, (int)g.per_xcd, off,
+                         srow, coef, dg, ChebStep{});
+  }
 }
 
 void onebody_rows(bool c64, const void* src, void* dst, const void* add, int64_t rows, int64_t cols,
