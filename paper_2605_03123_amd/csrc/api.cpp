@@ -241,8 +241,10 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
       int w = std::atoi(e);
       if (w >= 1 && w < P->W) P->W = w;
     }
-    // upload ring
-    P->slot_bytes = (size_t)6 << 20;
+    // Upload ring.  A slot holds all parameters of a program, so its size bounds
+    // the steps of a time evolution: phases alone (h = 0) take an 80-byte stage
+    // and a 64-byte table job each, 58000 steps.
+    P->slot_bytes = (size_t)8 << 20;
     if (fault_hit("alloc") ||
         hipHostMalloc((void**)&P->h_ring, P->slot_bytes * ffx_plan_s::kSlots, hipHostMallocDefault) != hipSuccess)
       throw Error(FFX_ENOMEM, "pinned host allocation failed");

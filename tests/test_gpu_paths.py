@@ -130,3 +130,16 @@ def test_dense_rotation_of_small_sectors(ffx, norb, nelec, both):
     out = ffx.apply_orbital_rotation(v, U, norb, nelec, U_b=U_b)
     ref = og.apply_orbital_rotation(_ref(v), U, norb, nelec, U_b=U_b)
     assert np.max(np.abs(_ref(out) - ref)) <= TOL[torch.complex128]
+
+
+# the longest gate programs: every step of a time evolution is part of one program, whose stages and tables go up
+# together.  With h = 0 the steps are phases alone, the smallest stages with a table each; 50000 of them have to fit.
+# Every step rounds an amplitude by a few eps: 50000 x 8 eps = 1e-10.
+def test_program_of_many_phases(ffx):
+    norb, nelec, steps = 4, (2, 2), 50000
+    r = synth.rng([61])
+    v = _state(r, norb, nelec, torch.complex128)
+    J = synth.random_symmetric(r, norb, 0.5)
+    out = ffx.simulate_trotter_diag_coulomb(v, np.zeros((norb, norb)), J, 5.0, norb, nelec, n_steps=steps)
+    ref = og.apply_diag_coulomb_evolution(_ref(v), J, 5.0, norb, nelec)
+    assert np.max(np.abs(_ref(out) - ref)) <= 1e-10
