@@ -667,7 +667,13 @@ int ffx_apply_orbital_rotation(ffx_plan plan, void* vec, const double* U_a, cons
       throw Error(FFX_EINVAL, "non-finite U");
     DeviceGuard dg(plan->device);
     hipStream_t s = as_stream(stream);
-    if (plan->takes_dense()) {
+    auto has_zero = [&](const double* U) {
+      for (int i = 0; U && i < N * N; ++i)
+        if (U[2 * i] == 0.0 && U[2 * i + 1] == 0.0) return true;
+      return false;
+    };
+    const bool any_u = std::max(plan->dim[0], plan->dim[1]) <= ffx_plan_s::kDenseAnyU;
+    if (plan->takes_dense() && (any_u || !(has_zero(U_a) || has_zero(U_b)))) {
       // small sector: the dense form is the faster one (measured)
       check_rotation_args(N, U_a, U_b);
       rotate_dense(*plan, vec, U_a, U_b, plan->dense_ws, s);

@@ -133,9 +133,19 @@ struct ffx_plan_s {
   int* rank_hi = nullptr;
   bool rdm_pairs = false;  // transition one-body matrices from row pairs at any size
   // standalone orbital rotations of complex128 sectors with at most this many
-  // configurations per spin take the dense form on the matrix cores.  Device
-  // time of one rotation, dense against Givens sweeps: 12 and 57 us at 252
-  // configurations, 32 and 56 at 330, 64 and 57 at 462, 350 and 91 at 924.
+  // configurations per spin take the dense form on the matrix cores.  Whole
+  // call with a full complex (real) U, dense against Givens sweeps: 20 (20) and
+  // 53 (37) us at 252 configurations, 31 (31) and 69 (45) at 330, 44 (43) and 91
+  // (55) at 364 in 14 orbitals; from 462 on the sweeps are as fast (dense 64 us
+  // of device time against 57, 350 against 91 at 924).
+  // Above kDenseAnyU configurations a U with a zero entry keeps the sweeps:
+  // they skip the rotations that its structure saves, and an amplitude that is
+  // not finite stays with the configurations it is coupled to, where a product
+  // spreads it over the state (0 times NaN).  At 330 configurations in 11
+  // orbitals: identity 14 us, phases 24, a 3-orbital block 27, against 42 dense
+  // with 7 and 4 electrons; two blocks of half the orbitals 41 against 42 (41
+  // against 20 at 252).
+  static constexpr int64_t kDenseAnyU = 128;
   int64_t dense_max_dim = 384;
   void* dense_ws = nullptr;  // its compound matrices and intermediate
   bool takes_dense() const { return dim[0] <= dense_max_dim && dim[1] <= dense_max_dim; }

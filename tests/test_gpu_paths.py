@@ -143,3 +143,39 @@ def test_program_of_many_phases(ffx):
     out = ffx.simulate_trotter_diag_coulomb(v, np.zeros((norb, norb)), J, 5.0, norb, nelec, n_steps=steps)
     ref = og.apply_diag_coulomb_evolution(_ref(v), J, 5.0, norb, nelec)
     assert np.max(np.abs(_ref(out) - ref)) <= 1e-10
+
+
+def _structured(r, norb, kind):
+    """Unitaries with entries that are exactly zero."""
+    U = np.eye(norb, dtype=np.complex128)
+    if kind == "phases":
+        return np.diag(np.exp(1j * r.normal(size=norb)))
+    if kind == "permutation":
+        return U[r.permutation(norb)]
+    if kind == "block":
+        U[2:6, 2:6] = synth.random_unitary(r, 4)
+    return U
+
+
+# which rotations take the dense form: full U up to 384 configurations per spin (bit for bit the explicit call), not
+# one spin above it, and above 128 no U with zeros (bit for bit the sweeps, also around an amplitude that is not finite)
+@pytest.mark.parametrize("norb,nelec,dense", [(9, (4, 4), True), (10, (5, 5), True), (11, (4, 3), True),
+                                              (11, (5, 5), False), (11, (5, 1), False), (11, (1, 5), False)])
+@pytest.mark.parametrize("kind", ["full", "identity", "phases", "permutation", "block"])
+def test_which_rotations_take_the_dense_form(ffx, monkeypatch, norb, nelec, dense, kind):
+    r = synth.rng([67, norb, nelec[0], nelec[1]])
+    v = _state(r, norb, nelec, torch.complex128)
+    U = synth.random_unitary(r, norb) if kind == "full" else _structured(r, norb, kind)
+    small = max(v.shape) <= 128
+    plan = ffx.Plan(norb, nelec, torch.complex128)
+    monkeypatch.setenv("FFX_DENSE", "0")
+    sweeps = ffx.Plan(norb, nelec, torch.complex128)
+    if not small and kind != "full":
+        v[1, 0] = complex(float("nan"), float("inf"))
+    out = ffx.apply_orbital_rotation(v, U, norb, nelec, plan=plan).cpu().numpy()
+    same = ffx.apply_orbital_rotation_dense if dense and (small or kind == "full") else ffx.apply_orbital_rotation
+    np.testing.assert_array_equal(out, same(v, U, norb, nelec, plan=sweeps).cpu().numpy())
+    # the same for the other spin's matrix alone
+    F = synth.random_unitary(r, norb)
+    out = ffx.apply_orbital_rotation(v, F, norb, nelec, U_b=U, plan=plan).cpu().numpy()
+    np.testing.assert_array_equal(out, same(v, F, norb, nelec, U_b=U, plan=sweeps).cpu().numpy())
