@@ -323,27 +323,12 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
     // a diagonal stage tabulates its cross term by bytes of the column string;
     // segments shorter than the tables evaluate it per element
     auto evaluates_directly = [&](int64_t longest) { return longest < 256 * ((norb + 7) / 8); };
-    // Threads of a block: the waves that the registers leave a compute unit
-    // (max_threads / 64), shared by the blocks that its LDS holds (or by the
-    // fewer that the launch has for it), and no more than the widest window's
-    // chunks or four elements a thread can use.  At 14 orbitals a row of
-    // complex128 leaves room for two blocks: 256-thread blocks, one to a unit
-    // with 32-bit member tables beside the row, ran 963 us per pass.
-    auto block_threads = [&](const std::vector<std::vector<SegWindowTable>>& tabs, size_t lds, int64_t blocks,
+    auto block_threads = [&](const std::vector<std::vector<SegWindowTable>>& tabs, size_t lds, int64_t rows, int n_seg,
                              int max_threads, int max_len) {
       size_t chunks = 1;
       for (const auto& ts : tabs)
         for (const SegWindowTable& t : ts) chunks = std::max(chunks, t.chunk_m.size());
-      const int64_t room = std::max<int64_t>(1, (int64_t)(160 * 1024 / std::max<size_t>(lds, 1)));
-      const int64_t per_cu = std::max<int64_t>(1, std::min(room, (blocks + cus - 1) / cus));
-      int64_t waves = std::max<int64_t>(1, max_threads / 64 / per_cu);
-      waves = std::min<int64_t>(waves, std::max<int64_t>((int64_t)chunks, (max_len + 255) / 256));
-      // a whole number of waves per SIMD, where blocks share a compute unit: a
-      // block's waves start at the first SIMD, so two blocks of 6 waves need
-      // four places there and only three exist (14 orbitals, complex
-      // rotations: 770 us per pass against 600 with 4 waves)
-      if (per_cu > 1 && waves > 4) waves = waves / 4 * 4;
-      int t = (int)waves * 64;
+      int t = seg_block_threads((int64_t)chunks, lds, rows, n_seg, cus, max_threads, max_len);
       if (const char* e = std::getenv("FFX_SEG_THREADS")) {  // block size override, for tuning
         const int v = std::atoi(e);
         if (v >= 64 && v <= 1024 && v % 64 == 0) t = v;
@@ -481,8 +466,9 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
       ss.n_seg = (int)segs.size();
       ss.max_len = 0;
       for (const auto& sg : segs) ss.max_len = std::max(ss.max_len, sg.second);
-      const int64_t n_blocks = P->dim[1 - s] * (int64_t)ss.n_seg;
-      ss.threads = block_threads(tabs, ss.lds, n_blocks, dev::seg_pass_max_threads(P->c64, ss.Wseg, false), ss.max_len);
+      const int64_t rows = P->dim[1 - s];
+      ss.threads =
+          block_threads(tabs, ss.lds, rows, ss.n_seg, dev::seg_pass_max_threads(P->c64, ss.Wseg, false), ss.max_len);
       std::vector<dev::SegDev> hsegs = upload_windows(segs, tabs, ss.Wseg, ss.threads, P->c64, &ss.max_mt);
       ss.lds = dev::seg_pass_lds(P->c64, norb, ss.max_len, ss.max_mt, ss.direct);
       // tables for real rotations, at window width 6 with the parts of an
@@ -498,8 +484,8 @@ int ffx_plan_create(ffx_plan* out, int norb, int na, int nb, ffx_dtype dtype, in
         real_words = std::max(real_words, mt.size() / 8);
       }
       ss.lds_real = dev::seg_pass_lds(P->c64, norb, ss.max_len, (int)real_words, ss.direct);
-      ss.threads_real =
-          block_threads(tabs, ss.lds_real, n_blocks, dev::seg_pass_max_threads(P->c64, ss.Wseg, split), ss.max_len);
+      ss.threads_real = block_threads(tabs, ss.lds_real, rows, ss.n_seg,
+                                      dev::seg_pass_max_threads(P->c64, ss.Wseg, split), ss.max_len);
       std::vector<dev::SegDev> hreal = upload_windows(segs, tabs, ss.Wseg, ss.threads_real, false, &ss.max_mt_real);
       // partner ranges of the crossing rotation on (wt - 1, wt): a segment whose
       // high part H lacks wt pairs its strings holding wt - 1 (the last C(wt-1,

@@ -674,6 +674,21 @@ std::vector<cd> dagger(int n, const std::vector<cd>& A) {
   return B;
 }
 
+int seg_block_threads(int64_t chunks, size_t lds, int64_t rows, int64_t n_seg, int cus, int max_threads, int max_len) {
+  const int64_t blocks = rows * n_seg;
+  const int64_t room = std::max<int64_t>(1, (int64_t)(160 * 1024 / std::max<size_t>(lds, 1)));
+  const int64_t per_cu = std::max<int64_t>(1, std::min(room, (blocks + cus - 1) / cus));
+  int64_t waves = std::max<int64_t>(1, max_threads / 64 / per_cu);
+  waves = std::min<int64_t>(waves, std::max<int64_t>(chunks, (max_len + 255) / 256));
+  // a whole number of waves per SIMD, where blocks share a compute unit: a
+  // block's waves start at the first SIMD, so two blocks of 6 waves need
+  // four places there and only three exist (14 orbitals, complex
+  // rotations: 770 us per pass against 600 with 4 waves)
+  if (per_cu > 1 && waves > 4) waves = waves / 4 * 4;
+  const int64_t most = (((int64_t)1 << 32) - 1) / ((rows + 7) / 8 * 8 * n_seg * 64);
+  return (int)std::max<int64_t>(1, std::min(waves, most)) * 64;
+}
+
 OneBodyGrid onebody_grid(int64_t rows, int64_t cols, int elem_bytes) {
   OneBodyGrid g;
   g.row_blocks = (rows + 3) / 4;

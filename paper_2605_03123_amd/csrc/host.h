@@ -196,6 +196,16 @@ struct OneBodyTable {
 };
 OneBodyTable build_one_body_table(int norb, const std::vector<uint64_t>& strs, const std::vector<double>& h);
 
+// Threads of a segment pass's block, one block for each of n_seg segments of
+// each row: the waves that the registers leave a compute unit (max_threads /
+// 64), shared by the blocks that its LDS holds (or by the fewer that the launch
+// has for it), and no more than the widest window's chunks or four elements a
+// thread can use.  At 14 orbitals a row of complex128 leaves room for two
+// blocks: 256-thread blocks, one to a unit with 32-bit member tables beside the
+// row, ran 963 us per pass.  Fewer where the launch (its rows rounded up to the
+// 8 XCDs) would reach 2^32 work-items.
+int seg_block_threads(int64_t chunks, size_t lds, int64_t rows, int64_t n_seg, int cus, int max_threads, int max_len);
+
 // The blocks of the one-body row kernel over a rows x cols state: each takes 4
 // rows and a tile of 64 columns.  A launch of blocks of 256 threads must stay
 // below 2^32 work-items (HIP's limit on a grid dimension), which is 2^32

@@ -53,6 +53,14 @@ int main() {
   onebody(binom(32, 5), binom(32, 4), 8);
   onebody(binom(32, 4), binom(32, 5), 16);
   onebody(binom(32, 10), binom(32, 2), 8);
+  // segment passes of long states: 29 orbitals (8, 3) in complex128, one block of 75 KB to a compute unit, and 31
+  // orbitals (10, 2) in complex64 with the tables of complex rotations; 14 orbitals (7, 7) keep their 512 threads
+  CHECK(seg_block_threads(60, 100 * 1024, binom(29, 8), 1, 256, 1024, 3654) * (binom(29, 8) + 7) < ((int64_t)1 << 32),
+        "segment pass of 29 orbitals (8, 3)");
+  CHECK(seg_block_threads(8, 31 * 1024, binom(31, 10), 1, 256, 1024, 465) * (binom(31, 10) + 7) < ((int64_t)1 << 32),
+        "segment pass of 31 orbitals (10, 2)");
+  CHECK(seg_block_threads(60, 70 * 1024, 3432, 1, 256, 1024, 3432) == 512, "segment pass of 14 orbitals (7, 7)");
+  CHECK(seg_block_threads(1, 4096, binom(32, 16), 1, 256, 1024, 1) == 64, "one wave at the least");
   if (fails) return 1;
   std::printf("grid checks passed\n");
   return 0;
