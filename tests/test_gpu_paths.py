@@ -179,3 +179,24 @@ def test_which_rotations_take_the_dense_form(ffx, monkeypatch, norb, nelec, dens
     F = synth.random_unitary(r, norb)
     out = ffx.apply_orbital_rotation(v, F, norb, nelec, U_b=U, plan=plan).cpu().numpy()
     np.testing.assert_array_equal(out, same(v, F, norb, nelec, U_b=U, plan=sweeps).cpu().numpy())
+
+
+# the Chebyshev step inside the one-body pass: one column tile, tiles per XCD and shared with a ragged last one, beta
+# rows in LDS and transposed; against the Taylor series of the same Hamiltonian
+@pytest.mark.parametrize("norb,nelec", [(9, (4, 2)), (13, (5, 5)), (14, (7, 4)), (24, (1, 4)), (20, (1, 6))])
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+def test_chebyshev_step_in_the_one_body_pass(ffx, monkeypatch, norb, nelec, dtype):
+    monkeypatch.setenv("FFX_ONEBODY", "direct")
+    r = synth.rng([71, norb, nelec[0], nelec[1]])
+    v = _state(r, norb, nelec, dtype)
+    ham, t = synth.hubbard_2d(norb, 1), 0.05
+    out, _ = ffx.evolve_exact(v, ham, t, norb, nelec, tol=1e-13)
+    Ha, Hb = (_hopping(ham.h, norb, n) for n in nelec)
+    na, nb = (ost.occupations(norb, n).astype(np.float64) for n in nelec)
+    two = 0.5 * ham.J[0, 0, 0] * (nelec[0] + nelec[1] + 2.0 * (na @ nb.T))
+    ref = term = _ref(v)
+    for k in range(1, 60):
+        term = (Ha @ term + (Hb @ term.T).T + two * term) * (-1j * t / k)
+        ref = ref + term
+    assert np.max(np.abs(term)) < 1e-16
+    assert np.max(np.abs(_ref(out) - ref)) <= TOL[dtype]
