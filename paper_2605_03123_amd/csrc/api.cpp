@@ -1061,7 +1061,7 @@ struct HamAction {
     int32_t* src = nullptr;
     double* coef = nullptr;
   } tab[2];
-  // beta rows that fit in LDS: that spin's table by columns (entry k of column
+  // beta rows held in LDS (onebody_cols_fits): that spin's table by columns (entry k of column
   // c at k * cols + c, cnt[c] of them) instead of tab[1]
   struct ColTab {
     int32_t* cnt = nullptr;

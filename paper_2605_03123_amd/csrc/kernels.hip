@@ -767,16 +767,26 @@ static void launch_onebody_cols(const void* src, void* dst, int64_t rows, int co
                                 const int32_t* scol, const double* coef, hipStream_t s) {
   using V = typename V2T<R>::type;
   auto k = k_onebody_cols<R, RB>;
-  (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  static const hipError_t attr =
+      hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  (void)attr;
   const int threads = std::min(512, (cols + 63) / 64 * 64);
   hipLaunchKernelGGL(k, dim3((unsigned)((rows + RB - 1) / RB)), dim3(threads), (size_t)RB * cols * sizeof(V), s,
                      (const V*)src, (V*)dst, rows, cols, cnt, scol, coef);
 }
 
 // Rows per block: as many as fit 64 KB (two blocks to a compute unit) while
-// the launch still has two blocks for each of 256 units; 0: a row exceeds LDS.
+// the launch still has two blocks for each of 256 units; 0: the rows go
+// through the transposed state instead.  That is so above 9600 columns (150 KB
+// of complex128) in both precisions: blocks of one long row read the whole
+// table, 12 bytes an entry, from the L2 for every row, 1 to 1.5 MB of it up to
+// there, 1.9 to 3.2 MB at 10626 and 15504 columns.  Exact evolution on
+// lattices, rows in LDS against the transposed state: complex128, 4845 columns
+// 14.2 and 18.5 ms, 8855 columns 37.8 and 47.9; complex64, 4845 columns 10.8 and
+// 11.6, 8855 columns 25.5 and 31.6, 10626 columns 13.2 and 12.3, 15504 columns
+// 130 and 110 (one H psi of it 19.4 and 14.4).
 static int onebody_cols_rows(size_t elem, int64_t rows, int64_t cols) {
-  if ((size_t)cols * elem > 150 * 1024) return 0;
+  if (cols > 9600) return 0;
   int rb = 1;
   while (rb < 8 && 2 * rb * cols * elem <= 64 * 1024 && rows >= 1024 * rb) rb *= 2;
   return rb;
