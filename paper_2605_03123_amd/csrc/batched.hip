@@ -55,10 +55,9 @@ struct BatchLds {
   double* red;     // 16 doubles
 };
 
-// LDS of a block: the rows, then red (16 doubles), then either the segment
-// tables (mt, wq, rowf: segment tasks) or acc (the other kinds).  A launch
-// that runs one kind allocates only that kind's part; the all-kinds kernels
-// lay both out, the tables first (kind = -1).
+// LDS of a block: the rows, then red (16 doubles), then acc, and in the
+// all-kinds kernels (kind = -1) the segment tables (mt, wq, rowf) before it.
+// A launch of segment tasks alone lays them out by task (seg_task_lds).
 constexpr int kRedDoubles = 16;
 constexpr int kAccDoubles = 4 * 2 * kBatchMaxOrb * kBatchMaxOrb;
 // doubles of the cross weights and row factors of a task of at most wq_rows rows
@@ -69,9 +68,7 @@ __host__ __device__ inline size_t seg_tab_doubles(int wq_rows) {
 __host__ __device__ inline size_t batch_lds_kind(int kind, int lds_row_bytes, int max_mt, int wq_rows) {
   const size_t tabs = (size_t)max_mt * 16 + seg_tab_doubles(wq_rows) * 8;
   const size_t head = (size_t)lds_row_bytes + (size_t)kRedDoubles * 8;
-  if (kind == BK_SEG) return head + tabs;
-  if (kind >= 0) return head + (size_t)kAccDoubles * 8;
-  return head + tabs + (size_t)kAccDoubles * 8;
+  return head + (kind < 0 ? tabs : 0) + (size_t)kAccDoubles * 8;
 }
 
 __device__ __forceinline__ BatchLds batch_lds_map(char* smem, const BatchDev& B, int kind = -1) {
@@ -79,25 +76,33 @@ __device__ __forceinline__ BatchLds batch_lds_map(char* smem, const BatchDev& B,
   L.rows = smem;
   L.red = (double*)(smem + B.lds_row_bytes);
   char* p = (char*)(L.red + kRedDoubles);
-  if (kind == BK_SEG || kind < 0) {
+  if (kind < 0) {
     L.mt = (int4*)p;
     L.wq = (double*)(L.mt + B.max_mt);
     L.rowf = L.wq + B.wq_rows * kBatchMaxOrb;
     p = (char*)(L.rowf + 2 * B.wq_rows);
   }
-  if (kind != BK_SEG) L.acc = (double*)p;
+  L.acc = (double*)p;
   return L;
 }
 
 // LDS of one segment task, laid out by its own rows and tables (a launch of
-// segment tasks takes its largest task's)
-__host__ __device__ inline int seg_rows_bytes(int elem, int rows, int64_t len) {
-  return (int)(((int64_t)rows * len * elem + 15) & ~(int64_t)15);
+// segment tasks takes its largest task's): byte offsets after the rows
+struct SegTaskLds {
+  int mt, wq, rowf, red, bytes;
+};
+__host__ __device__ inline SegTaskLds seg_task_lds(int elem, int rows, int64_t len, int n_mt) {
+  SegTaskLds L;
+  L.mt = (int)(((int64_t)rows * len * elem + 15) & ~(int64_t)15);
+  L.wq = L.mt + n_mt * 16;
+  L.rowf = L.wq + rows * kBatchMaxOrb * 8;
+  L.red = L.rowf + 2 * rows * 8;
+  L.bytes = L.red + kRedDoubles * 8;
+  return L;
 }
 
 size_t batch_seg_lds(bool c64, int rows, int64_t len, int n_mt) {
-  return (size_t)seg_rows_bytes(c64 ? 8 : 16, rows, len) + (size_t)n_mt * 16 +
-         (kRedDoubles + seg_tab_doubles(rows)) * 8;
+  return (size_t)seg_task_lds(c64 ? 8 : 16, rows, len, n_mt).bytes;
 }
 
 size_t batch_lds(bool c64, int lds_row_bytes, int max_mt, int wq_rows) {
@@ -802,11 +807,13 @@ __global__ __launch_bounds__(kind_threads(KIND), kind_waves(KIND, REAL, sizeof(R
     const int cs = ps.layout == 0 ? 1 : 0;
     const int RR = pick2(ty.rows_per_task, cs);
     BatchLds L{};
+    const SegTaskLds at = seg_task_lds((int)sizeof(typename V2T<R>::type), RR, pick2(ty.dim, cs),
+                                       REAL ? pick2(ty.n_mt_real, cs) : pick2(ty.n_mt_all, cs));
     L.rows = smem;
-    L.mt = (int4*)(smem + seg_rows_bytes((int)sizeof(typename V2T<R>::type), RR, pick2(ty.dim, cs)));
-    L.wq = (double*)(L.mt + (REAL ? pick2(ty.n_mt_real, cs) : pick2(ty.n_mt_all, cs)));
-    L.rowf = L.wq + RR * kBatchMaxOrb;
-    L.red = L.rowf + 2 * RR;
+    L.mt = (int4*)(smem + at.mt);
+    L.wq = (double*)(smem + at.wq);
+    L.rowf = (double*)(smem + at.rowf);
+    L.red = (double*)(smem + at.red);
     seg_task<W, REAL, R>(B.passes + lo, B.types + ps.type, task, L);
   }
   if constexpr (KIND == BK_INNER) inner_task<R>(ps, ty, task, batch_lds_map(smem, B, KIND).red);

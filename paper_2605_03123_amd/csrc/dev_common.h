@@ -531,11 +531,12 @@ __device__ __forceinline__ void lds_put(const zc128& v, uint32_t a) {
 __device__ __forceinline__ void lds_put(const zc64& v, uint32_t a) { *(FFX_LDS lds_f2*)(uintptr_t)a = lds_f2{v.x, v.y}; }
 
 // A class: C(W, M) members, M = electrons in the window.  base, moff: the LDS
-// byte addresses that its members count from and of its offset table.  The
-// table (three words for the widest class) stays in registers from the loads
-// to the stores.  (32-bit offsets, four to a word, took 5 + 5 word reads per
-// 20-member class, read again before the stores since 20 registers could not
-// be held: half as many LDS bytes as the members' own of a row plane.)
+// byte addresses that its members count from and of its offset table.  With
+// HOLD (lanes that hold one part of an amplitude) the table, three words for
+// the widest class, stays in registers from the loads to the stores; row planes
+// and complex rotations have no registers for it (10 spills in planes) and read
+// it again.  (32-bit offsets, four to a word, took 5 + 5 word reads per
+// 20-member class: half as many LDS bytes as the members' own of a row plane.)
 template <int W, int M, bool REAL, class V, int S, int ES, bool HOLD, int... K>
 __device__ __forceinline__ void lds_class(uint32_t base, uint32_t moff, const RotLane<ER<V>>& rl, int nrot,
                                           std::integer_sequence<int, K...>) {

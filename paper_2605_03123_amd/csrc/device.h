@@ -119,16 +119,16 @@ void dist2(bool c64, const void* x, const void* y, int64_t n, double* partials, 
 int sample_blocks(int64_t n);
 int sample_state(bool c64, const void* vec, int64_t n, double* bs, double* pre, const double* u, int64_t n_samples,
                  int64_t* out, hipStream_t stream);
-// Dense form of an orbital rotation: C[J, I] = det U[J, I] over the n-electron
-// configurations (masks, d of them; U complex norb x norb, device), and the
-// complex128 product Y = A B on the FP64 matrix cores (A row-major with leading
-// dimension lda; element (k, n) of B at B[k * sbk + n * sbn]; Y row-major, ldy).
-// Both spins' compound matrices; U comes from the device (dU[k]) or, null there
-// and norb <= compound_arg_orbitals(), from the host (hU[k], read by the call).
-// C[0] == C[1]: one matrix for both, spin 0's.
+// Dense form of an orbital rotation: for both spins k, C[k][J, I] = det U_k[J, I]
+// over its n[k]-electron configurations (masks[k], d[k] of them).  U_k (complex
+// norb x norb) comes from the device (dU[k]) or, null there and norb <=
+// compound_arg_orbitals(), from the host (hU[k], read by the call).  C[0] ==
+// C[1]: one matrix for both, spin 0's.
 int compound_arg_orbitals();
 void compound_matrices(const uint32_t* const masks[2], const int64_t d[2], const int n[2], int norb,
                        const double* const hU[2], const double* const dU[2], void* const C[2], hipStream_t s);
+// The complex128 product Y = A B on the FP64 matrix cores (A row-major with leading dimension lda; element (k, n) of B
+// at B[k * sbk + n * sbn]; Y row-major, ldy).
 void zgemm_mfma(const void* A, int64_t lda, const void* B, int64_t sbk, int64_t sbn, void* Y, int64_t ldy, int M,
                 int N, int K, hipStream_t s);
 // The allocation-free sampler's block sums and prefix live in a static device
@@ -162,7 +162,7 @@ void onebody_rows(bool c64, const void* src, void* dst, const void* add, int64_t
                   const int64_t* off, const int32_t* srow, const double* coef, const OneBodyDiag& dg,
                   const ChebStep* ch, hipStream_t stream);
 // dst[r, c] = sum_{k < cnt[c]} coef[k * cols + c] * src[r, scol[k * cols + c]]; dst must not alias src.  For rows
-// that fit in LDS (onebody_cols_fits).
+// that are held in LDS (onebody_cols_fits).
 bool onebody_cols_fits(bool c64, int64_t rows, int64_t cols);
 void onebody_cols(bool c64, const void* src, void* dst, int64_t rows, int64_t cols, const int32_t* cnt,
                   const int32_t* scol, const double* coef, hipStream_t stream);
