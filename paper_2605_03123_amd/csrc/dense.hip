@@ -5,8 +5,8 @@
 // 20 n (N - n) d^2 flops against this form's 16 d^3, so it is taken
 // for small sectors only, where both are bound by latency.
 //   * k_compound<n>: one thread per entry, the n x n minor gathered into registers and reduced by
-//     Gaussian elimination with partial pivoting in complex FP64; both spins in one launch where their
-//     electron numbers are n or n + 1.
+//     Gaussian elimination with partial pivoting in complex FP64; both spins in one launch where that
+//     costs nothing.
 //   * Y = A B (complex128, row-major A and Y, B addressed through two strides so that C^T needs no
 //     copy) by v_mfma_f64_16x16x4, the real and imaginary accumulators of a 16 x 16 tile taking four
 //     products per k step: k_zgemm_tile for small products, k_zgemm_mfma for large ones.
@@ -14,6 +14,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <cstdlib>
 #include <cstring>
 
 #include "dev_common.h"
@@ -34,6 +35,7 @@ struct CompoundSpin {
 struct CompoundArgs {
   CompoundSpin sp[2];
   int norb;
+  int per;       // entries of a thread
   int which[2];  // the matrix in u that spin blockIdx.y takes
   double u[2][2 * kArgOrb * kArgOrb];
 };
@@ -110,7 +112,10 @@ __device__ __forceinline__ zc128 minor_det(uint32_t mj, uint32_t mi, int norb, c
   }
 }
 
-template <int LO>
+// Minors of LO or (HI = LO + 1) of either size.  The kernel of two sizes has the
+// registers of the larger one (152 for 7 and 8, 120 for 7 alone): 860 us per
+// matrix of 7 electrons at d = 3432, 630 us with 7 alone.
+template <int LO, int HI>
 __global__ __launch_bounds__(256) void k_compound(CompoundArgs) {
   extern __shared__ double su[];
   // (through the argument segment's address: indexed by lane, the struct itself would be copied to scratch)
@@ -120,14 +125,24 @@ __global__ __launch_bounds__(256) void k_compound(CompoundArgs) {
   const double* U = sp.U ? sp.U : P->u[P->which[blockIdx.y]];
   for (int i = threadIdx.x; i < 2 * norb * norb; i += 256) su[i] = U[i];
   __syncthreads();
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x, d = sp.d;
-  if (idx >= d * d) return;
-  const int64_t J = idx / d, I = idx - J * d;
-  const uint32_t mj = sp.masks[J], mi = sp.masks[I];
-  sp.C[idx] = sp.n == LO ? minor_det<LO>(mj, mi, norb, su) : minor_det<LO + 1>(mj, mi, norb, su);
+  const int64_t d = sp.d;
+  int64_t idx = (int64_t)blockIdx.x * P->per * 256 + threadIdx.x;
+  for (int k = P->per; k > 0 && idx < d * d; --k, idx += 256) {
+    const int64_t J = idx / d, I = idx - J * d;
+    const uint32_t mj = sp.masks[J], mi = sp.masks[I];
+    if (LO == HI || sp.n == LO)
+      sp.C[idx] = minor_det<LO>(mj, mi, norb, su);
+    else
+      sp.C[idx] = minor_det<HI>(mj, mi, norb, su);
+  }
 }
 
 int compound_arg_orbitals() { return kArgOrb; }
+
+// Spins of different electron numbers share a launch while all its blocks fit
+// the chip at once (two of 256 threads to a compute unit for each spin), where
+// the launch is what counts.
+constexpr int64_t kSharedEntries = 2 * 256 * 256;
 
 void compound_matrices(const uint32_t* const masks[2], const int64_t d[2], const int n[2], int norb,
                        const double* const hU[2], const double* const dU[2], void* const C[2], hipStream_t s) {
@@ -138,30 +153,52 @@ void compound_matrices(const uint32_t* const masks[2], const int64_t d[2], const
     a.which[k] = k;
     if (!dU[k]) std::memcpy(a.u[k], hU[k], sizeof(double) * 2 * norb * norb);
   }
-  auto launch = [&](const CompoundArgs& q, int lo, int64_t dm, int spins) {
-    const dim3 g((unsigned)((dm * dm + 255) / 256), (unsigned)spins), b(256);
-    const size_t lds = sizeof(double) * 2 * norb * norb;
-    switch (lo) {
-      case 0: hipLaunchKernelGGL(k_compound<0>, g, b, lds, s, q); break;
-      case 1: hipLaunchKernelGGL(k_compound<1>, g, b, lds, s, q); break;
-      case 2: hipLaunchKernelGGL(k_compound<2>, g, b, lds, s, q); break;
-      case 3: hipLaunchKernelGGL(k_compound<3>, g, b, lds, s, q); break;
-      case 4: hipLaunchKernelGGL(k_compound<4>, g, b, lds, s, q); break;
-      case 5: hipLaunchKernelGGL(k_compound<5>, g, b, lds, s, q); break;
-      case 6: hipLaunchKernelGGL(k_compound<6>, g, b, lds, s, q); break;
-      default: hipLaunchKernelGGL(k_compound<7>, g, b, lds, s, q); break;
+  const size_t lds = sizeof(double) * 2 * norb * norb;
+  auto grid = [&](int64_t dm, int spins) {
+    // several entries to a thread where blocks abound: each stages all of U
+    const int64_t groups = (dm * dm + 255) / 256;
+    a.per = groups >= 4 * 4096 ? 4 : 1;
+    return dim3((unsigned)((groups + a.per - 1) / a.per), (unsigned)spins);
+  };
+  auto one = [&](int size, int64_t dm, int spins) {
+    const dim3 g = grid(dm, spins), b(256);
+    switch (size) {
+      case 0: hipLaunchKernelGGL((k_compound<0, 0>), g, b, lds, s, a); break;
+      case 1: hipLaunchKernelGGL((k_compound<1, 1>), g, b, lds, s, a); break;
+      case 2: hipLaunchKernelGGL((k_compound<2, 2>), g, b, lds, s, a); break;
+      case 3: hipLaunchKernelGGL((k_compound<3, 3>), g, b, lds, s, a); break;
+      case 4: hipLaunchKernelGGL((k_compound<4, 4>), g, b, lds, s, a); break;
+      case 5: hipLaunchKernelGGL((k_compound<5, 5>), g, b, lds, s, a); break;
+      case 6: hipLaunchKernelGGL((k_compound<6, 6>), g, b, lds, s, a); break;
+      case 7: hipLaunchKernelGGL((k_compound<7, 7>), g, b, lds, s, a); break;
+      default: hipLaunchKernelGGL((k_compound<8, 8>), g, b, lds, s, a); break;
     }
   };
-  const int lo = std::min(std::min(n[0], n[1]), 7);
+  auto two = [&](int lo, int64_t dm) {
+    const dim3 g = grid(dm, 2), b(256);
+    switch (lo) {
+      case 0: hipLaunchKernelGGL((k_compound<0, 1>), g, b, lds, s, a); break;
+      case 1: hipLaunchKernelGGL((k_compound<1, 2>), g, b, lds, s, a); break;
+      case 2: hipLaunchKernelGGL((k_compound<2, 3>), g, b, lds, s, a); break;
+      case 3: hipLaunchKernelGGL((k_compound<3, 4>), g, b, lds, s, a); break;
+      case 4: hipLaunchKernelGGL((k_compound<4, 5>), g, b, lds, s, a); break;
+      case 5: hipLaunchKernelGGL((k_compound<5, 6>), g, b, lds, s, a); break;
+      case 6: hipLaunchKernelGGL((k_compound<6, 7>), g, b, lds, s, a); break;
+      default: hipLaunchKernelGGL((k_compound<7, 8>), g, b, lds, s, a); break;
+    }
+  };
+  const int64_t dmax = std::max(d[0], d[1]);
   if (C[0] == C[1]) {
-    launch(a, lo, d[0], 1);
-  } else if (std::max(n[0], n[1]) <= lo + 1) {
-    launch(a, lo, std::max(d[0], d[1]), 2);
+    one(n[0], d[0], 1);
+  } else if (n[0] == n[1]) {
+    one(n[0], dmax, 2);
+  } else if (std::abs(n[0] - n[1]) == 1 && dmax * dmax <= kSharedEntries) {
+    two(std::min(n[0], n[1]), dmax);
   } else {
-    launch(a, std::min(n[0], 7), d[0], 1);
+    one(n[0], d[0], 1);
     a.sp[0] = a.sp[1];
     a.which[0] = 1;
-    launch(a, std::min(n[1], 7), d[1], 1);
+    one(n[1], d[1], 1);
   }
 }
 
