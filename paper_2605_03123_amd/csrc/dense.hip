@@ -329,9 +329,12 @@ __global__ __launch_bounds__(256) void k_zgemm_mfma(const zc128* __restrict__ A,
       }
 }
 
-// 64 x 64 tiles once they fill the compute units (924^3, 225 tiles: 158 us in
-// them, 152 us in 16 x 16 tiles; above, the smaller tiles read operands too often)
-constexpr unsigned kTileBlocks = 256;
+// 64 x 64 tiles once they fill the compute units, nine in ten of them: above, the
+// smaller tiles read operands too often.  A rotation's two products, 16 x 16
+// against 64 x 64 tiles: 225 tiles (924 x 924) 307 and 336 us, 195 tiles (924 x
+// 792) 274 and 306, 192 tiles (364 x 2002) 412 and 416; 246 tiles (325 x 2600) 608
+// and 524, 252 tiles (715 x 1287) 428 and 370, 256 tiles (1001 x 1001) 451 and 361.
+constexpr unsigned kTileBlocks = 230;
 
 void zgemm_mfma(const void* A, int64_t lda, const void* B, int64_t sbk, int64_t sbn, void* Y, int64_t ldy, int M,
                 int N, int K, hipStream_t s) {
