@@ -200,3 +200,21 @@ def test_chebyshev_step_in_the_one_body_pass(ffx, monkeypatch, norb, nelec, dtyp
         ref = ref + term
     assert np.max(np.abs(term)) < 1e-16
     assert np.max(np.abs(_ref(out) - ref)) <= TOL[dtype]
+
+
+# the explicit dense form of large sectors: matrices whose threads take several entries, spins that share a launch and
+# that do not, products on both sides of the line between small and large tiles; against the Givens sweeps
+@pytest.mark.parametrize("norb,nelec", [(10, (5, 4)), (11, (5, 4)), (12, (6, 6)), (13, (4, 8)), (14, (1, 7)),
+                                        (14, (7, 6)), (25, (3, 2))])
+@pytest.mark.parametrize("both", [True, False])
+def test_dense_rotation_of_large_sectors(ffx, norb, nelec, both):
+    r = synth.rng([73, norb, nelec[0], nelec[1]])
+    v = _state(r, norb, nelec, torch.complex128)
+    U = synth.random_unitary(r, norb)
+    U_b = synth.random_unitary(r, norb) if both else None
+    a = ffx.apply_orbital_rotation_dense(v, U, norb, nelec, U_b=U_b)
+    b = ffx.apply_orbital_rotation(v, U, norb, nelec, U_b=U_b)
+    if max(v.shape) <= 384:
+        assert torch.equal(a, b)
+        b = torch.from_numpy(og.apply_orbital_rotation(_ref(v), U, norb, nelec, U_b=U_b)).to(v.device)
+    assert float((a - b).abs().max()) <= TOL[torch.complex128]
